@@ -13,7 +13,7 @@ A case is a dict of plain values.  ``op`` names the entry point:
                  (``solve_logk``)
 * ``homogenize`` apparent conductivities of several microstructures in one batch (``homogenize``)
 
-Sizes are nodes per axis.  The face sets: ``dirichlet`` (six Dirichlet faces), ``x`` (Dirichlet
+Sizes are nodes per axis, ``edge`` the length of the box's edges.  The face sets: ``dirichlet`` (six Dirichlet faces), ``x`` (Dirichlet
 x faces, zero flux elsewhere: the two-phase and homogenisation problems) and ``robin`` (Dirichlet
 x faces, du/dn + u = g elsewhere: convective walls).
 """
@@ -34,7 +34,7 @@ SOLVE_RTOL = 1e-13
 
 
 def _case(op, n, **kw):
-    c = {"op": op, "nx": n[0], "ny": n[1], "nz": n[2], "prec": "f64", "bc": "x"}
+    c = {"op": op, "nx": n[0], "ny": n[1], "nz": n[2], "prec": "f64", "bc": "x", "edge": 1.0}
     c.update(kw)
     return c
 
@@ -65,7 +65,7 @@ def listed():
         # the inverse problem's step: forward and adjoint solve
         _case("gradient", (33, 33, 33), name="gradient f64 33"),
         # microstructures of three sizes under three load cases each
-        _case("homogenize", (33, 49, 65), prec="mixed", name="homogenize mixed 33-65"),
+        _case("homogenize", (49, 57, 65), prec="mixed", name="homogenize mixed 49-65"),
     ]
 
 
@@ -86,6 +86,13 @@ def _sizes(rng, lo, hi):
 
 
 def draw(rng):
+    c = _draw(rng)
+    if c["op"] != "homogenize":
+        c["edge"] = round(rng.uniform(0.5, 2.0), 3)
+    return c
+
+
+def _draw(rng):
     op = rng.choices(["reduced", "transpose", "full", "derivative", "precond", "prolong", "jacobian", "solve",
                       "gradient", "homogenize"], [8, 2, 2, 1, 3, 2, 1, 3, 1, 1])[0]
     bc = rng.choice(["x", "dirichlet", "robin"])
@@ -106,7 +113,7 @@ def draw(rng):
         return _case("solve", _sizes(rng, 17, 129), prec=rng.choice(["f64", "mixed"]))
     if op == "gradient":
         return _case("gradient", _sizes(rng, 17, 65))
-    return _case("homogenize", tuple(rng.choice([17, 25, 33, 41, 49, 57, 65]) for _ in range(3)), prec="mixed")
+    return _case("homogenize", tuple(_log_int(rng, 17, 49) for _ in range(3)), prec="mixed")
 
 
 # --- inputs ---------------------------------------------------------------------------------
@@ -185,7 +192,7 @@ def prepare(case, seed):
         s["opts"] = api.SolveOptions(precond=True, rtol=SOLVE_RTOL)
         return s
     bc, robin = _faces(case["bc"])
-    s["plan"] = api.Plan(n, bc=bc, precision=case["prec"], device=DEV, robin=robin)
+    s["plan"] = api.Plan(n, hi=(case["edge"],) * 3, bc=bc, precision=case["prec"], device=DEV, robin=robin)
     if op == "apply":
         s["y"] = torch.empty_like(s["u"])
     elif op == "derivative":
@@ -193,7 +200,8 @@ def prepare(case, seed):
     elif op == "precond":
         s["out"] = torch.empty_like(s["r"])
     elif op == "prolong":
-        s["coarse"] = api.Plan((case["cx"], case["cy"], case["cz"]), bc=bc, precision=case["prec"], device=DEV)
+        s["coarse"] = api.Plan((case["cx"], case["cy"], case["cz"]), hi=(case["edge"],) * 3, bc=bc,
+                               precision=case["prec"], device=DEV)
         s["uf"] = torch.empty(n, device=DEV, dtype=F64)
     elif op == "jacobian":
         s["y"] = torch.empty_like(s["v"])
@@ -258,8 +266,8 @@ def work(case):
 
 # --- the same results in 64 bits, in plain torch ---------------------------------------------
 
-def _diff(n):
-    """Collocation derivative at the ascending Chebyshev-Gauss-Lobatto points of [0, 1]."""
+def _diff(n, edge):
+    """Collocation derivative at the ascending Chebyshev-Gauss-Lobatto points of [0, edge]."""
     N = n - 1
     i = np.arange(n)
     th = np.pi / (2 * N)
@@ -268,15 +276,15 @@ def _diff(n):
     D = (c[:, None] / c[None, :]) / np.where(dx == 0.0, 1.0, dx)
     D[i, i] = 0.0
     D[i, i] = -D.sum(axis=1)
-    return 2.0 * D
+    return (2.0 / edge) * D
 
 
 class _Axis:
     """D; L: interior values -> the pencil with its end values from the homogeneous face rows;
     M = D L; E: the interior rows of D; A = E M."""
 
-    def __init__(self, n, bc, sigma):
-        D = _diff(n)
+    def __init__(self, n, edge, bc, sigma):
+        D = _diff(n, edge)
         N = n - 1
         self.rows = np.zeros((2, n))  # the face rows, Dirichlet: the value itself
         rows = [(-D[0], sigma[0], 0), (D[N], sigma[1], N)]
@@ -317,7 +325,7 @@ def _keep(x, a):
 def _axes(case, bc=None):
     f, r = _faces(case["bc"])
     f = bc or f
-    return [_Axis(n, f[2 * a:2 * a + 2], r[2 * a:2 * a + 2]) for a, n in enumerate(_n(case))]
+    return [_Axis(n, case["edge"], f[2 * a:2 * a + 2], r[2 * a:2 * a + 2]) for a, n in enumerate(_n(case))]
 
 
 def _reduced(ax, K, x):
@@ -463,7 +471,7 @@ def exact(case, seed):
         f = _reduced if case["mode"] == "reduced" else _transposed
         return _pad(f(ax, s["K"], s["u"][1:-1, 1:-1, 1:-1].contiguous()))
     if op == "derivative":
-        return _along(torch.from_numpy(_diff(_n(case)[case["axis"]])).to(DEV), s["u"], case["axis"])
+        return _along(torch.from_numpy(_diff(_n(case)[case["axis"]], case["edge"])).to(DEV), s["u"], case["axis"])
     if op == "precond":
         return _pad(_Fdm(_axes(case))(s["r"][1:-1, 1:-1, 1:-1].contiguous(), KC))
     if op == "prolong":
@@ -486,7 +494,7 @@ def exact(case, seed):
             cols = []
             for a in range(3):
                 bc, _ = api.load_case((m, m, m), a, "cpu")
-                ax = _axes({"nx": m, "ny": m, "nz": m, "bc": "x"}, bc)
+                ax = _axes({"nx": m, "ny": m, "nz": m, "edge": 1.0, "bc": "x"}, bc)
                 g = [None] * 3
                 g[a] = (0.0, 1.0)
                 u, _, _ = _solved(ax, K, torch.zeros_like(K), g)

@@ -78,7 +78,7 @@ extern "C" {
 #define CHEB_APPLY_TRANSPOSE 2u /* with REDUCED: y = (A_kk + A_kr G)^T u_k */
 
 /* operator route of the reduced apply and its transpose (cheb_plan_set_route) */
-#define CHEB_ROUTE_AUTO 0   /* matrix-core route on axes with N in {16,32,48,64,96,128}, FFT route elsewhere */
+#define CHEB_ROUTE_AUTO 0   /* matrix-core route on axes with N <= 256, FFT route beyond */
 #define CHEB_ROUTE_FFT 1    /* DCT-I through the FFT of the even extension on every axis */
 #define CHEB_ROUTE_MATRIX 2 /* matrix-core route wherever N allows it (as AUTO) */
 
@@ -135,8 +135,8 @@ typedef struct cheb_plan cheb_plan;
  * coefficient with CHEB_ERR_SINGULAR_BC.  `stream` is a
  * hipStream_t (NULL = default stream).  Allocates a few KB of device constants
  * (boundary rows of the differentiation matrix), the matrix-core route's
- * fragment tables when an axis has N <= 128, and, when all three axes can take
- * that route and axes x and y have the same N, one field-sized buffer
+ * fragment tables when an axis has N <= 256, and, when all three axes can take
+ * that route, one field-sized buffer
  * (n0*n1*n2 values, 4 bytes each for CHEB_F32 plans, 8 otherwise) that holds
  * the second partial sum of an apply whose x and y passes share one launch
  * (if that allocation fails, applies take three launches instead).
@@ -179,13 +179,13 @@ int cheb_plan_set_robin_nodes(cheb_plan* plan, const double* sigma_faces);
  *   CHEB_ROUTE_FFT    -- the DCT-I of each pencil through the FFT of its even
  *                        extension, coefficient recurrence, back-transform
  *                        (Algorithm 1 / Section 2.2), any N;
- *   CHEB_ROUTE_MATRIX -- for N in {16, 32, 48, 64, 96, 128}: the derivative as a
- *                        dense contraction with the collocation matrix on the
- *                        matrix cores (even-odd split), other axes use the FFT;
+ *   CHEB_ROUTE_MATRIX -- for N <= 256: the derivative as a dense contraction with
+ *                        the collocation matrix on the matrix cores (even-odd
+ *                        split), other axes use the FFT;
  *   CHEB_ROUTE_AUTO   -- the default; currently identical to CHEB_ROUTE_MATRIX.
- * The two routes agree to rounding.  FULL applies, derivatives and the adjoint
- * gradient always use the FFT route; the Newton Jacobian's derivative term
- * follows the plan's route like the reduced operator.  Returns
+ * The two routes agree to rounding.  FULL applies, derivatives, the adjoint
+ * gradient and the Newton Jacobian follow the plan's route like the reduced
+ * operator.  Returns
  * CHEB_ERR_INVALID_ARG for an unknown route. */
 int cheb_plan_set_route(cheb_plan* plan, int32_t route);
 
@@ -198,17 +198,17 @@ int cheb_plan_set_route(cheb_plan* plan, int32_t route);
  * plans).  report (host, may be NULL when report_len is 0) receives up to 4
  * values: microseconds per apply for [FFT route, matrix tile shape 0, matrix
  * tile shape 1] (-1 where not applicable) and the index chosen.  Synchronises
- * the plan's stream.  Without this call AUTO uses tile shape 1 (the faster one
- * at every N measured, both precisions). */
+ * the plan's stream.  Without this call AUTO uses tile shape 1. */
 int cheb_plan_autotune(cheb_plan* plan, int32_t field_precision, const void* K, const void* u, void* y,
                        double* report, int32_t report_len);
 
-/* Tile shape of the matrix-core route for one precision, on every axis:
- * 0 = 8-wave workgroups with the derivative's fragment table in LDS, 1 = 4-wave
- * workgroups with each wave's fragments in registers (the two shapes the
- * autotuner times).  field_precision: CHEB_F64 or CHEB_F32 (the passes that run
- * in that type).  Returns CHEB_ERR_INVALID_ARG for another precision or shape;
- * affects only the matrix-core route. */
+/* Tile shape of the matrix-core route's reduced passes for one precision, on
+ * every axis with N <= 128 (longer axes have one shape): 0 = 8-wave workgroups
+ * (one copy of the derivative's fragment table serves eight 16-pencil tasks),
+ * 1 = 4-wave workgroups (the two shapes the autotuner times).
+ * field_precision: CHEB_F64 or CHEB_F32 (the passes that run in that type).
+ * Returns CHEB_ERR_INVALID_ARG for another precision or shape; affects only the
+ * matrix-core route. */
 int cheb_plan_set_tile_shape(cheb_plan* plan, int32_t field_precision, int32_t shape);
 
 int cheb_plan_destroy(cheb_plan* plan);

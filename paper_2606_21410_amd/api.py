@@ -111,9 +111,9 @@ class Plan:
         self.route = route
 
     def set_tile_shape(self, shape: int, precision: str = "f64"):
-        """Tile shape of the matrix-core route for the passes that run in
-        ``precision`` ('f64' or 'f32'): 0 = 8-wave workgroups with the fragment
-        table in LDS, 1 = 4-wave workgroups with register fragments."""
+        """Tile shape of the matrix-core route for the reduced passes that run in
+        ``precision`` ('f64' or 'f32') on axes with N <= 128: 0 = 8-wave
+        workgroups, 1 = 4-wave workgroups."""
         L.check(self.lib.cheb_plan_set_tile_shape(self._h, _PREC[precision], int(shape)))
 
     def capture_applies(self, K, us, ys, mode: str = "reduced"):

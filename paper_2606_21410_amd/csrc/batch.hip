@@ -857,7 +857,7 @@ int cheb_batch_create(const cheb_grid* grids, int32_t nprob, int32_t precision, 
       g.rep = s;
       g.members.push_back(s);
       const cheb_plan* p = B->plans[s];
-      g.dense = p->dd_ok[0] && p->dd_ok[1] && p->dd_ok[2] && p->ax[0].N == p->ax[1].N && p->ax[1].N == p->ax[2].N;
+      g.dense = p->dd_ok[0] && p->dd_ok[1] && p->dd_ok[2];
       B->groups.push_back(g);
     }
     bool pplaced = false;

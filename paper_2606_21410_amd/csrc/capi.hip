@@ -437,7 +437,7 @@ int cheb_plan_set_tile_shape(cheb_plan* plan, int32_t field_precision, int32_t s
     return CHEB_ERR_INVALID_ARG;
   }
   if (shape != 0 && shape != 1) {
-    set_error("tile shape must be 0 (8-wave, LDS table) or 1 (4-wave, register fragments)");
+    set_error("tile shape must be 0 (8-wave workgroups) or 1 (4-wave workgroups)");
     return CHEB_ERR_INVALID_ARG;
   }
   const int pi = field_precision == CHEB_F64 ? 0 : 1;

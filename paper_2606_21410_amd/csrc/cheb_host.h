@@ -17,11 +17,14 @@ namespace cheb {
 inline void dense_D(int N, double L, std::vector<double>& D) {
   const int n = N + 1;
   D.assign((size_t)n * n, 0.0);
-  auto offdiag = [N](int i, int j) {
+  // sin(pi k / 2N), k <= 2N
+  std::vector<double> sn(2 * N + 1);
+  for (int k = 0; k <= 2 * N; ++k) sn[k] = std::sin(M_PI * k / (2.0 * N));
+  auto offdiag = [N, &sn](int i, int j) {
     const double ci = (i == 0 || i == N) ? 2.0 : 1.0;
     const double cj = (j == 0 || j == N) ? 2.0 : 1.0;
     const double sgn = ((i + j) % 2 == 0) ? 1.0 : -1.0;
-    const double dif = 2.0 * std::sin(M_PI * (i + j) / (2.0 * N)) * std::sin(M_PI * (i - j) / (2.0 * N));
+    const double dif = 2.0 * sn[i + j] * (i > j ? sn[i - j] : -sn[j - i]);
     return (ci / cj) * sgn / dif;
   };
   for (int i = 0; 2 * i <= N; ++i) {

@@ -86,6 +86,7 @@ struct cheb_plan {
   int route;
   int dd_ok[3];
   size_t dd_off[3][2];
+  int dd_mt[3];         // row blocks of the axis' tables (dense_pass.h)
   int dense_var[3][2];  // tile shape of the matrix-core pass, [axis][f64, f32]
   int auto_fft[2];      // CHEB_ROUTE_AUTO resolved to the FFT route, [f64, f32] (autotuner)
   hipEvent_t kev[2];    // LGMRES: completion of the last two enqueued Arnoldi steps (created on first use)
@@ -105,8 +106,8 @@ struct cheb_plan {
   float* rn32;
   double rn_mean[6];
   // the two-axis launch's second output: one field (n0 n1 n2 values of the
-  // plan's widest precision), allocated at creation when axes 0 and 1 have
-  // the same N on the matrix-core route; null otherwise
+  // plan's widest precision), allocated at creation when all three axes can
+  // take the matrix-core route; null otherwise
   void* pair_buf;
 };
 
@@ -132,39 +133,33 @@ int launch_axis_pass(const cheb_plan* p, int axis, int mode, int first, const T*
 template <typename T>
 int apply_t(const cheb_plan* p, const T* K, const T* u, T* y, int mode, hipStream_t s);
 
-// ---- matrix-core route (dense_f64.hip / dense_f32.hip) ----
+// ---- matrix-core route (dense.hip) ----
 int dense_setup(cheb_plan* p);
 struct DenseSys;
-// batched reduced pass over the systems act[0..nact) of the table sys (same N,
-// box and tile shape as `rep`); K, u, y are packed bases
+// batched reduced pass over the systems act[0..nact) of the table sys (same n
+// and box as `rep`); K, u, y are packed bases
 template <typename T>
 int launch_dense_batch(const cheb_plan* rep, int axis, int first, const T* K, const T* u, T* y,
                        const DenseSys* sys, const int* act, int nact, hipStream_t s);
-// transpose: 0 reduced pass, 1 transposed reduced pass.  yadd: a second
-// partial sum that the accumulating pass along the unit-stride axis (axis 2,
-// first = 0) adds, and only that pass (null otherwise)
+// one axis pass on the matrix cores.  mode: LineMode (dense_pass.h); transpose
+// picks the table of D^T (LINE_TRANSP and transposed derivatives); c: the
+// coefficient of LINE_JAC, null otherwise; first: y is initialised, else added
+// to (not along z)
 template <typename T>
-int launch_dense_pass(const cheb_plan* p, int axis, int transpose, int first, const T* K, const T* u, T* y,
-                      const T* yadd, hipStream_t s);
-// the first passes along axes 0 and 1 in one launch, into y0 and y1; possible
-// when all three axes take the matrix-core route, axes 0 and 1 have the same N
-// and tile shape, and the plan holds pair_buf (dense_pair_ok)
+int launch_line_pass(const cheb_plan* p, int axis, int mode, int transpose, int first, const T* K, const T* c,
+                     const T* u, T* y, hipStream_t s);
+// the three passes of one apply (mode LINE_REDUCED, LINE_TRANSP, LINE_FULL or,
+// with c[axis], LINE_JAC) when every axis takes the matrix-core route: x and y
+// in one launch where the plan holds pair_buf, then z adding both
 template <typename T>
-bool dense_pair_ok(const cheb_plan* p);
-// y += D_a (c .* L v) on interior nodes (the Newton Jacobian's k'(T) term on
-// the matrix-core route; FP64)
-template <typename T>
-int launch_dense_dacc(const cheb_plan* p, int axis, const T* c, const T* v, T* y, hipStream_t s);
-// the Newton Jacobian's action in the two launches of the reduced apply (the
-// c_a terms in the flux epilogues); CHEB_ERR_UNSUPPORTED when the plan cannot
-template <typename T>
-int launch_dense_jac(const cheb_plan* p, const T* K, const T* const* c, const T* v, T* y, hipStream_t s);
-template <typename T>
-int launch_dense_pair(const cheb_plan* p, int transpose, const T* K, const T* u, T* y0, T* y1, hipStream_t s);
+int launch_line_apply(const cheb_plan* p, int mode, const T* K, const T* const* c, const T* u, T* y, hipStream_t s);
 // pi: 0 for the FP64 passes, 1 for the FP32 passes
 inline bool use_dense(const cheb_plan* p, int axis, int pi) {
   if (!p->dd_ok[axis] || p->route == CHEB_ROUTE_FFT) return false;
   return p->route == CHEB_ROUTE_MATRIX || !p->auto_fft[pi];
+}
+inline bool use_dense_all(const cheb_plan* p, int pi) {
+  return use_dense(p, 0, pi) && use_dense(p, 1, pi) && use_dense(p, 2, pi);
 }
 
 // offset (entries) in rn64 / rn32 of axis a's per-pencil end-block inverses:

@@ -1,6 +1,7 @@
 // Instantiation and dispatch of the axis-pass kernel for one precision.
 #pragma once
 
+#include "dense_pass.h"
 #include "internal.h"
 #include "pass_kernel.h"
 
@@ -83,13 +84,22 @@ inline const double* robin_nodes<double>(const cheb_plan* p) { return p->rn64; }
 template <>
 inline const float* robin_nodes<float>(const cheb_plan* p) { return p->rn32; }
 
+// the matrix-core pass that stands for a mode of this one
+static int line_mode(int mode) {
+  switch (mode) {
+    case MODE_FULL: return LINE_FULL;
+    case MODE_REDUCED: return LINE_REDUCED;
+    case MODE_TRANSPOSE: return LINE_TRANSP;
+    default: return LINE_DERIV;  // MODE_DERIV, MODE_DERIV_T (the transposed table)
+  }
+}
+
 template <typename T>
 int launch_axis_pass(const cheb_plan* p, int axis, int mode, int first, const T* K, const T* u, T* y,
                      hipStream_t s) {
-  if ((mode == MODE_REDUCED || mode == MODE_TRANSPOSE) && use_dense(p, axis, sizeof(T) == sizeof(double) ? 0 : 1))
-    return launch_dense_pass<T>(p, axis, mode == MODE_TRANSPOSE ? 1 : 0, first, K, u, y, nullptr, s);
-  if constexpr (sizeof(T) == sizeof(double)) {
-    if (mode == MODE_DERIV_ACC && !first && use_dense(p, axis, 0)) return launch_dense_dacc<T>(p, axis, K, u, y, s);
+  if (mode != MODE_DERIV_ACC && use_dense(p, axis, sizeof(T) == sizeof(double) ? 0 : 1)) {
+    const int tr = mode == MODE_TRANSPOSE || mode == MODE_DERIV_T ? 1 : 0;
+    return launch_line_pass<T>(p, axis, line_mode(mode), tr, first, K, nullptr, u, y, s);
   }
   PassArgs<T> a;
   a.gate = p->gate;
@@ -120,16 +130,8 @@ int launch_axis_pass(const cheb_plan* p, int axis, int mode, int first, const T*
 
 template <typename T>
 int apply_t(const cheb_plan* p, const T* K, const T* u, T* y, int mode, hipStream_t s) {
-  if ((mode == MODE_REDUCED || mode == MODE_TRANSPOSE) && dense_pair_ok<T>(p)) {
-    // matrix-core route: the x and y passes in one launch (x into y, y into
-    // the plan's second buffer; each initialises every row it owns), then the
-    // z pass adds both to its own
-    const int tr = mode == MODE_TRANSPOSE ? 1 : 0;
-    T* y1 = (T*)p->pair_buf;
-    int rc = launch_dense_pair<T>(p, tr, K, u, y, y1, s);
-    if (rc) return rc;
-    return launch_dense_pass<T>(p, 2, tr, 0, K, u, y, y1, s);
-  }
+  if (use_dense_all(p, sizeof(T) == sizeof(double) ? 0 : 1))
+    return launch_line_apply<T>(p, line_mode(mode), K, nullptr, u, y, s);
   // z pass first (it initialises every row it owns), then y, then x
   int rc = launch_axis_pass<T>(p, 2, mode, 1, K, u, y, s);
   if (rc) return rc;

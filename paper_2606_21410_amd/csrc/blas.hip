@@ -221,13 +221,16 @@ __global__ void k_picard_coeff(double* K, const double* K0, const double* u, siz
 // reciprocal law of the nonlinear example: k = K0 / (1 + alpha T) and
 // k' = -alpha K0 / (1 + alpha T)^2 = -alpha k / (1 + alpha T)
 __global__ void k_newton_coeff(double* k, double* kp, const double* K0, const double* T, double alpha,
-                               size_t npts) {
+                               size_t npts, int* flag) {
+  int bad = 0;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < npts; i += (size_t)gridDim.x * blockDim.x) {
     const double d = 1.0 + alpha * T[i];
     const double kv = K0[i] / d;
     k[i] = kv;
     kp[i] = -alpha * kv / d;
+    if (!(kv > 0.0) || !isfinite(kv)) bad = 1;
   }
+  if (bad) atomicOr(flag, 1);
 }
 
 __global__ void k_vmul(double* y, const double* a, const double* b, size_t npts) {
@@ -399,9 +402,9 @@ int picard_coeff(double* K, const double* K0, const double* u, size_t npts, hipS
   return hip_check(hipGetLastError(), "picard_coeff");
 }
 
-int newton_coeff(double* k, double* kp, const double* K0, const double* T, double alpha, size_t npts,
+int newton_coeff(double* k, double* kp, const double* K0, const double* T, double alpha, size_t npts, int* dflag,
                  hipStream_t s) {
-  hipLaunchKernelGGL(k_newton_coeff, dim3(grid_for(npts)), dim3(kThreads), 0, s, k, kp, K0, T, alpha, npts);
+  hipLaunchKernelGGL(k_newton_coeff, dim3(grid_for(npts)), dim3(kThreads), 0, s, k, kp, K0, T, alpha, npts, dflag);
   return hip_check(hipGetLastError(), "newton_coeff");
 }
 

@@ -91,7 +91,7 @@ const float* robin_array<float>(const cheb_plan* p) { return p->rn32; }
 // the launch fields of one axis: tables, lift entries, per-node inverses, output
 template <typename T>
 LineAxis<T> line_axis(const cheb_plan* p, int axis, int mode, int transpose, bool batch, T* y, T* yb) {
-  const bool all = mode == LINE_FULL || mode == LINE_DERIV;  // every pencil, not only the interior ones
+  const bool all = mode == LINE_FULL || mode == LINE_DERIV || mode == LINE_DMUL;  // every pencil, not only the interior ones
   LineAxis<T> x;
   x.tab = line_table_of<T>(p, axis, transpose);
   x.y = y;

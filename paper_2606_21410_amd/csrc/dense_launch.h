@@ -15,7 +15,7 @@ template <typename T, int MT, int MODE, bool FIRST, bool CG>
 static int launch_line_inst(const LineArgs<T>& a, hipStream_t s) {
   constexpr int lds = line_lds_bytes<T>(MT);
   static_assert(lds <= 64 * 1024, "matrix-core tile exceeds the default LDS limit");
-  constexpr bool ALLP = MODE == LINE_FULL || MODE == LINE_DERIV;
+  constexpr bool ALLP = MODE == LINE_FULL || MODE == LINE_DERIV || MODE == LINE_DMUL;
   static DeviceCache cache;
   int dev = 0;
   if (int rc = current_device(&dev)) return rc;
@@ -69,7 +69,7 @@ static int launch_line_inst(const LineArgs<T>& a, hipStream_t s) {
 template <typename T, int MT, int MODE>
 static int launch_line_g(const LineArgs<T>& a, int first, hipStream_t s) {
   const bool cg = a.ax[0].axis == 2;
-  if constexpr (MODE == LINE_DERIV) {
+  if constexpr (MODE == LINE_DERIV || MODE == LINE_DMUL) {
     return cg ? launch_line_inst<T, MT, MODE, true, true>(a, s) : launch_line_inst<T, MT, MODE, true, false>(a, s);
   } else {
     if (first)
@@ -85,7 +85,7 @@ template <typename T, int MT, int MODE, bool FIRST, bool CG, int NW>
 static int launch_wave_inst(LineArgs<T>& a, hipStream_t s) {
   constexpr int lds = wave_lds_bytes<T>(MT, NW, CG);
   static_assert(lds <= 160 * 1024, "fragment table exceeds LDS");
-  constexpr bool ALLP = MODE == LINE_FULL || MODE == LINE_DERIV;
+  constexpr bool ALLP = MODE == LINE_FULL || MODE == LINE_DERIV || MODE == LINE_DMUL;
   static DeviceCache cache;
   int dev = 0;
   if (int rc = current_device(&dev)) return rc;
@@ -127,7 +127,7 @@ static int launch_wave_inst(LineArgs<T>& a, hipStream_t s) {
 template <typename T, int MT, int MODE, int NW>
 static int launch_wave_g(LineArgs<T>& a, int first, hipStream_t s) {
   const bool cg = a.ax[0].axis == 2;
-  if constexpr (MODE == LINE_DERIV) {
+  if constexpr (MODE == LINE_DERIV || MODE == LINE_DMUL) {
     return cg ? launch_wave_inst<T, MT, MODE, true, true, NW>(a, s) : launch_wave_inst<T, MT, MODE, true, false, NW>(a, s);
   } else {
     if (first)
@@ -149,8 +149,13 @@ static int launch_wave_nw(LineArgs<T>& a, int mode, int first, hipStream_t s) {
     case LINE_DERIV: return launch_wave_g<T, MT, LINE_DERIV, 4>(a, first, s);
     case LINE_JAC:
       if constexpr (sizeof(T) == sizeof(double)) return launch_wave_g<T, MT, LINE_JAC, 4>(a, first, s);
-    default: set_error("matrix-core pass: bad mode"); return CHEB_ERR_INVALID_ARG;
+      break;
+    case LINE_DMUL:
+      if constexpr (sizeof(T) == sizeof(double)) return launch_wave_g<T, MT, LINE_DMUL, 4>(a, first, s);
+      break;
   }
+  set_error("matrix-core pass: bad mode");
+  return CHEB_ERR_INVALID_ARG;
 }
 
 template <typename T, int MT>
@@ -165,8 +170,13 @@ int launch_line_mt(LineArgs<T>& a, int mode, int first, int shape, hipStream_t s
       case LINE_DERIV: return launch_line_g<T, MT, LINE_DERIV>(a, first, s);
       case LINE_JAC:
         if constexpr (sizeof(T) == sizeof(double)) return launch_line_g<T, MT, LINE_JAC>(a, first, s);
-      default: set_error("matrix-core pass: bad mode"); return CHEB_ERR_INVALID_ARG;
+        break;
+      case LINE_DMUL:
+        if constexpr (sizeof(T) == sizeof(double)) return launch_line_g<T, MT, LINE_DMUL>(a, first, s);
+        break;
     }
+    set_error("matrix-core pass: bad mode");
+    return CHEB_ERR_INVALID_ARG;
   }
 }
 

@@ -11,6 +11,7 @@
 //   LINE_FULL     y_int (+)= [ D (K .* (D u)) ]_int, and the face rows' values
 //                 at the end nodes the axis owns (all pencils)
 //   LINE_DERIV    y = D u, or D^T u with the transposed table (all pencils)
+//   LINE_DMUL     y = K .* D u (all pencils; FP64)
 // The derivative of a tile of pencils is a small dense contraction, so it runs
 // on the matrix cores: D cut into 16-row blocks, one block per wave, its
 // fragments in that wave's registers for the whole launch.
@@ -48,7 +49,7 @@
 
 namespace cheb {
 
-enum LineMode { LINE_REDUCED = 0, LINE_TRANSP = 1, LINE_JAC = 2, LINE_FULL = 3, LINE_DERIV = 4 };
+enum LineMode { LINE_REDUCED = 0, LINE_TRANSP = 1, LINE_JAC = 2, LINE_FULL = 3, LINE_DERIV = 4, LINE_DMUL = 5 };
 
 constexpr int kLineMaxN = 256;  // 8 row blocks
 constexpr int kLineMaxMT = 8;
@@ -239,7 +240,8 @@ template <typename T, int MT, int MODE, bool FIRST, bool CG>
 __global__ __launch_bounds__(64 * MT, line_waves<T>(MT)) void k_line_pass(LineArgs<T> a) {
   if (a.gate && !*a.gate) return;
   typedef typename Mfma<T>::v4 V4;
-  constexpr bool FULL = MODE == LINE_FULL, DER = MODE == LINE_DERIV, JAC = MODE == LINE_JAC;
+  constexpr bool FULL = MODE == LINE_FULL, DMUL = MODE == LINE_DMUL, DER = MODE == LINE_DERIV || DMUL;
+  constexpr bool JAC = MODE == LINE_JAC;
   constexpr bool LIFT = MODE == LINE_REDUCED || MODE == LINE_JAC;  // in-pencil lift after the first product
   constexpr bool TRA = MODE == LINE_TRANSP;
   constexpr bool ALLP = FULL || DER;   // every pencil, end values of u included
@@ -564,7 +566,7 @@ __global__ __launch_bounds__(64 * MT, line_waves<T>(MT)) void k_line_pass(LineAr
     };
 
     product([&](int ks) {
-      if (!DER && ks < 4) load_k(ks);
+      if ((!DER || DMUL) && ks < 4) load_k(ks);
     });
 
     if (DER) {
@@ -573,11 +575,11 @@ __global__ __launch_bounds__(64 * MT, line_waves<T>(MT)) void k_line_pass(LineAr
         const int b = cb[CG ? r : 0], i = node_of(r);
         if (b >= 0 && i < RM) {
           const T s = acco[r], d = acce[r];
-          dense_ref(py, b + __mul24(i, st)) = s + d;
-          if (2 * i != N) dense_ref(py, b + __mul24(N - i, st)) = s - d;
+          dense_ref(py, b + __mul24(i, st)) = DMUL ? (s + d) * klo[r] : s + d;
+          if (2 * i != N) dense_ref(py, b + __mul24(N - i, st)) = DMUL ? (s - d) * khi[r] : s - d;
         }
       }
-      if (midv && lc < C && lg == 0 && bmid0 >= 0) dense_ref(py, bmid) = mid;
+      if (midv && lc < C && lg == 0 && bmid0 >= 0) dense_ref(py, bmid) = DMUL ? mid * kmid : mid;
       if (more) {
         const Sys s = system_of(nxt);
 #pragma unroll

@@ -247,8 +247,8 @@ template <typename T>
 int mask_interior(T* y, const int* n, hipStream_t s);
 // K-dependent pointwise kernels
 int picard_coeff(double* K, const double* K0, const double* u, size_t npts, hipStream_t s);
-// k = K0 / (1 + alpha T), kp = dk/dT
-int newton_coeff(double* k, double* kp, const double* K0, const double* T, double alpha, size_t npts,
+// k = K0 / (1 + alpha T), kp = dk/dT; sets *dflag where k is not finite and positive
+int newton_coeff(double* k, double* kp, const double* K0, const double* T, double alpha, size_t npts, int* dflag,
                  hipStream_t s);
 int vmul(double* y, const double* a, const double* b, size_t npts, hipStream_t s);  // y = a * b (y may alias)
 int grad_accumulate(double* g, const double* du, const double* dl, int first, size_t npts,

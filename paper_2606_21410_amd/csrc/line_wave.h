@@ -52,7 +52,8 @@ template <typename T, int MT, int MODE, bool FIRST, bool CG, int NW>
 __global__ __launch_bounds__(64 * NW, wave_simd_waves<T>(MT, MODE, NW)) void k_line_wave(LineArgs<T> a) {
   if (a.gate && !*a.gate) return;
   typedef typename Mfma<T>::v4 V4;
-  constexpr bool FULL = MODE == LINE_FULL, DER = MODE == LINE_DERIV, JAC = MODE == LINE_JAC;
+  constexpr bool FULL = MODE == LINE_FULL, DMUL = MODE == LINE_DMUL, DER = MODE == LINE_DERIV || DMUL;
+  constexpr bool JAC = MODE == LINE_JAC;
   constexpr bool LIFT = MODE == LINE_REDUCED || MODE == LINE_JAC, TRA = MODE == LINE_TRANSP;
   constexpr bool ALLP = FULL || DER;   // every pencil, end values of u included
   constexpr bool YADD = CG && !FIRST;  // the last pass of a two-axis apply adds yadd
@@ -294,7 +295,7 @@ __global__ __launch_bounds__(64 * NW, wave_simd_waves<T>(MT, MODE, NW)) void k_l
     // first product, K's loads under it
     T klo[KS], khi[KS], kmid = T(0);
     product([&](int ks) __attribute__((always_inline)) {
-      if (DER) return;
+      if (DER && !DMUL) return;
       if (ks < KS) {
         klo[ks] = at(pk, ks / 4, ks % 4, false);
         khi[ks] = at(pk, ks / 4, ks % 4, true);
@@ -327,6 +328,7 @@ __global__ __launch_bounds__(64 * NW, wave_simd_waves<T>(MT, MODE, NW)) void k_l
         }
         if (FULL && m == 0 && i == 0) continue;
         T x = lo[r], y = hi[r];
+        if (DMUL) x *= klo[4 * m + r], y *= khi[4 * m + r];  // (the loads are in the stores' order)
         if (!FIRST) x += ylo[FIRST ? 0 : 4 * m + r], y += yhi[FIRST ? 0 : 4 * m + r];
         if (YADD) x += zlo[YADD ? (4 * m + r) % 8 : 0], y += zhi[YADD ? (4 * m + r) % 8 : 0];
         dense_ref(py, olo) = x;
@@ -342,7 +344,7 @@ __global__ __launch_bounds__(64 * NW, wave_simd_waves<T>(MT, MODE, NW)) void k_l
         for (int r = 0; r < 4; ++r) lo[r] = acco[m][r] + acce[m][r], hi[r] = acco[m][r] - acce[m][r];
         store(m, lo, hi);
       }
-      if (midv && valid && lk == 0) dense_ref(py, b0 + __mul24(half, st)) = mid;
+      if (midv && valid && lk == 0) dense_ref(py, b0 + __mul24(half, st)) = DMUL ? mid * kmid : mid;
     } else {
       // the first product's rows 0 and N, at the lanes lk = 0, broadcast over lk
       T u0 = T(0), uN = T(0);

@@ -483,8 +483,7 @@ int solve_plain(cheb_plan* p, const T* K, const T* bt, T* x, T* r, KrylovWS<T>& 
 
 // Newton iteration for k(x, T) = K0(x) / (1 + alpha T) (Section 3.4).  Fields of
 // the caller's work array, each padded to 256 bytes: k(T), c_a = k'(T) D_a T for
-// a = 0, 1, 2, the lifted direction (also k'(T) while linearising) and a
-// 256-byte flag slot.
+// a = 0, 1, 2, k'(T) and a 256-byte flag slot.
 constexpr int kNewtonFields = 5;
 
 struct NewtonWS {
@@ -502,26 +501,43 @@ NewtonWS newton_ws(const cheb_plan* p, void* work) {
   return w;
 }
 
-// k and c_a at the state T (full nodal array); fails when 1 + alpha T <= 0
-// somewhere, where the law has no positive conductivity.
-int newton_linearise(cheb_plan* p, const double* K0, double alpha, const double* T, NewtonWS& w) {
-  int rc = newton_coeff(w.k, w.V, K0, T, alpha, p->npts, p->stream);
-  for (int a = 0; a < 3 && !rc; ++a) {
-    rc = launch_axis_pass<double>(p, a, 3, 1, nullptr, T, w.c[a], p->stream);
-    if (!rc) rc = vmul(w.c[a], w.c[a], w.V, p->npts, p->stream);
-  }
+// k(T), k'(T) (into V) and the check of k at the state T (full nodal array), the
+// check's result on its way to the host behind event kev[0]
+int newton_coefficients(cheb_plan* p, const double* K0, double alpha, const double* T, NewtonWS& w) {
+  int rc = ensure_events(p);
   if (!rc) rc = hip_check(hipMemsetAsync(w.flag, 0, sizeof(int), p->stream), "hipMemsetAsync");
-  if (!rc) rc = check_positive_finite(w.k, p->npts, w.flag, p->stream);
+  if (!rc) rc = newton_coeff(w.k, w.V, K0, T, alpha, p->npts, w.flag, p->stream);
+  if (!rc)
+    rc = hip_check(hipMemcpyAsync(p->hpinned + 3 * 256, w.flag, sizeof(int), hipMemcpyDeviceToHost, p->stream),
+                   "hipMemcpyAsync");
+  if (!rc) rc = hip_check(hipEventRecord(p->kev[0], p->stream), "hipEventRecord");
+  return rc;
+}
+
+// fails when 1 + alpha T <= 0 somewhere, where the law has no positive conductivity
+int newton_checked(cheb_plan* p) {
+  int rc = hip_check(hipEventSynchronize(p->kev[0]), "hipEventSynchronize");
   if (rc) return rc;
-  int* hf = (int*)(p->hpinned + 3 * 256);
-  rc = hip_check(hipMemcpyAsync(hf, w.flag, sizeof(int), hipMemcpyDeviceToHost, p->stream), "hipMemcpyAsync");
-  if (!rc) rc = hip_check(hipStreamSynchronize(p->stream), "hipStreamSynchronize");
-  if (rc) return rc;
-  if (*hf) {
+  if (*(const int*)(p->hpinned + 3 * 256)) {
     set_error("k(T) = K0 / (1 + alpha T) must be finite and positive at every node (check K0 and 1 + alpha T)");
     return CHEB_ERR_BAD_INPUT;
   }
   return CHEB_OK;
+}
+
+// c_a = k'(T) D_a T: on the matrix-core route the derivative pass multiplies as
+// it stores
+int newton_directions(cheb_plan* p, const double* T, NewtonWS& w) {
+  int rc = CHEB_OK;
+  for (int a = 0; a < 3 && !rc; ++a) {
+    if (use_dense(p, a, 0)) {
+      rc = launch_line_pass<double>(p, a, LINE_DMUL, 0, 1, w.V, nullptr, T, w.c[a], p->stream);
+    } else {
+      rc = launch_axis_pass<double>(p, a, 3, 1, nullptr, T, w.c[a], p->stream);
+      if (!rc) rc = vmul(w.c[a], w.c[a], w.V, p->npts, p->stream);
+    }
+  }
+  return rc;
 }
 
 // y = J(T) v on interior rows (boundary rows 0): the reduced operator with
@@ -899,7 +915,8 @@ int cheb_newton_residual(cheb_plan* plan, const void* K0, double alpha, const vo
   if (rc) return rc;
   cheb_plan* p = plan;
   NewtonWS w = newton_ws(p, work);
-  rc = newton_linearise(p, (const double*)K0, alpha, (const double*)T, w);
+  rc = newton_coefficients(p, (const double*)K0, alpha, (const double*)T, w);
+  if (!rc) rc = newton_checked(p);
   if (!rc) rc = newton_neg_residual(p, w, (const double*)T, (const double*)f, (double*)r);
   if (!rc) rc = copy_scale<double>((double*)r, (const double*)r, -1.0, p->npts, p->stream);
   if (!rc) rc = hip_check(hipStreamSynchronize(p->stream), "hipStreamSynchronize");
@@ -916,7 +933,9 @@ int cheb_newton_jacobian(cheb_plan* plan, const void* K0, double alpha, const vo
   if (rc) return rc;
   cheb_plan* p = plan;
   NewtonWS w = newton_ws(p, work);
-  rc = newton_linearise(p, (const double*)K0, alpha, (const double*)T, w);
+  rc = newton_coefficients(p, (const double*)K0, alpha, (const double*)T, w);
+  if (!rc) rc = newton_directions(p, (const double*)T, w);
+  if (!rc) rc = newton_checked(p);  // before the first write to y
   if (!rc) rc = newton_jv(p, w, (const double*)v, (double*)y);
   if (!rc) rc = hip_check(hipStreamSynchronize(p->stream), "hipStreamSynchronize");
   return rc;
@@ -953,7 +972,8 @@ int cheb_newton(cheb_plan* plan, const void* K0, double alpha, const void* f, co
   double rref = 0.0, rn = 0.0;
   int rc2 = fill<double>(w64.r, 0.0, p->npts, s);
   if (!rc2) rc2 = lift_full<double>(p, w64.r, (const double*)g_faces, s);
-  if (!rc2) rc2 = newton_linearise(p, (const double*)K0, alpha, w64.r, w);
+  if (!rc2) rc2 = newton_coefficients(p, (const double*)K0, alpha, w64.r, w);
+  if (!rc2) rc2 = newton_checked(p);
   if (!rc2) rc2 = newton_neg_residual(p, w, w64.r, (const double*)f, w64.bt);
   if (!rc2) rc2 = vnorm<double>(p, w64.bt, w64.sc, &rref);
   if (rc2) return rc2;
@@ -965,7 +985,8 @@ int cheb_newton(cheb_plan* plan, const void* K0, double alpha, const void* f, co
   int nsteps = 0;
   const double stop = newton_tol * rref;
   for (int m = 0; !rc; ++m) {
-    rc = newton_linearise(p, (const double*)K0, alpha, T, w);
+    rc = newton_coefficients(p, (const double*)K0, alpha, T, w);
+    if (!rc) rc = newton_checked(p);
     if (!rc) rc = newton_neg_residual(p, w, T, (const double*)f, w64.bt);
     if (!rc) rc = vnorm<double>(p, w64.bt, w64.sc, &rn);
     if (rc) break;
@@ -977,7 +998,8 @@ int cheb_newton(cheb_plan* plan, const void* K0, double alpha, const void* f, co
     }
     if (m >= max_steps) break;
     double kc = 1.0;
-    if (sp.precond) rc = mean_K<double>(p, w.k, w64.sc, &kc);
+    rc = newton_directions(p, T, w);
+    if (!rc && sp.precond) rc = mean_K<double>(p, w.k, w64.sc, &kc);
     if (!rc) rc = fill<double>(w64.x, 0.0, p->npts, s);
     if (rc) break;
     auto J = [&](const double* in, double* out) { return newton_jv(p, w, in, out); };

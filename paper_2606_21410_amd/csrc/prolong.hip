@@ -2,98 +2,199 @@
 // pencil gives its Chebyshev coefficients, the coefficients are zero-padded to
 // the fine degree and the fine pencil is their cosine sum at the fine CGL
 // nodes.  z, then y, then x: (nc,nc,nc) -> (nc,nc,nf) -> (nc,nf,nf) -> (nf,nf,nf).
-// Both transforms are evaluated as direct cosine sums from LDS tables; the
-// prolongation runs once per refinement level, far off the solver's hot loop.
+//
+// The three steps along an axis are one matrix P (nf x nc) with a closed form
+// (the coefficient sums are Dirichlet kernels; theta_i = pi i / Nf, phi_j = pi j / Nc)
+//   P_ij = (-1)^j sin(Nc theta_i) sin(theta_i)
+//          / (Nc c_j 2 sin((theta_i + phi_j) / 2) sin((theta_i - phi_j) / 2)),
+// c_j = 2 at the two ends, 1 inside, and 1 where theta_i = phi_j.  It is
+// centro-symmetric, so it runs as an even-odd split contraction on the matrix
+// cores (FP64 for both field types): with e_j = u_j + u_{Nc-j} and
+// o_j = u_j - u_{Nc-j},
+//   (Pu)_i = s_i + d_i, (Pu)_{Nf-i} = s_i - d_i,
+//   s_i = sum_j (P_ij + P_{i,Nc-j}) / 2 e_j,  d_i = sum_j (P_ij - P_{i,Nc-j}) / 2 o_j.
+// A workgroup forms the fragments of 32 or 48 row pairs in LDS (two sines of
+// exact integer fractions and a division per entry pair, so the entries keep
+// their relative accuracy where nodes nearly meet) and its waves run tasks of 16
+// pencils over them, the pencils read straight from memory.  65^3 -> 129^3 in
+// FP64 takes 41 us, where direct cosine sums on the vector ALUs took 166 us
+// (129^3 -> 257^3: 185 and 1495 us, 17^3 -> 33^3: 15.5 both); what is left is three launches, each
+// with its table (about 3 us) and one or two rounds of tasks against 5 us of HBM
+// traffic and 4 us of matrix-core time in all.  Largest error against long
+// double arithmetic over sizes 9 to 129: 1.3e-15 of the largest value, the
+// sums' 1.5e-15.
 #include <cmath>
 #include <mutex>
 
+#include "dev_common.h"
 #include "internal.h"
 
 namespace cheb {
 
 namespace {
 
-constexpr int kPP = 16;    // pencils per tile
-constexpr int kPT = 256;   // threads
+constexpr int kPW = 4;      // waves per workgroup
+constexpr int kPWG = 512;   // workgroups of a launch: 768 and 1024 (more tables formed) take up to 3 us longer at 129^3
 
-__device__ __forceinline__ void pencil_geom(int axis, int p, const int* n, long long* base, long long* stride) {
+__device__ __forceinline__ void pencil_geom(int axis, int p, const int* n, size_t* base, int* stride) {
   if (axis == 2) {
-    *base = (long long)p * n[2];
+    *base = (size_t)p * n[2];
     *stride = 1;
   } else if (axis == 1) {
     const int ia = p / n[2], ib = p - ia * n[2];
-    *base = (long long)ia * n[1] * n[2] + ib;
+    *base = (size_t)ia * n[1] * n[2] + ib;
     *stride = n[2];
   } else {
     *base = p;
-    *stride = (long long)n[1] * n[2];
+    *stride = n[1] * n[2];
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(kPT) void k_prolong_axis(const T* __restrict__ src, T* __restrict__ dst, int axis,
-                                                     int s0, int s1, int s2, int d0, int d1, int d2) {
+// RB: 16-row blocks of row pairs per workgroup
+constexpr int prolong_lds_bytes(int Nc, int RB) {
+  return (32 * RB + (8 + RB * 128) * ((Nc / 2 + 4) / 4)) * (int)sizeof(double);
+}
+
+template <typename T, int RB>
+__global__ __launch_bounds__(64 * kPW) void k_prolong_axis(const T* __restrict__ src, T* __restrict__ dst, int axis,
+                                                          int s0, int s1, int s2, int d0, int d1, int d2) {
   extern __shared__ __align__(16) unsigned char smem[];
+  typedef Mfma<double>::v4 V4;
   const int ns[3] = {s0, s1, s2}, nd[3] = {d0, d1, d2};
   const int Nc = ns[axis] - 1, Nf = nd[axis] - 1;
-  const int nc = Nc + 1, nf = Nf + 1;
   const int npen = axis == 2 ? s0 * s1 : axis == 1 ? s0 * s2 : s1 * s2;
-  double* cc = (double*)smem;            // cos(pi j / Nc), j < 2 Nc
-  double* cf = cc + 2 * Nc;              // cos(pi j / Nf), j < 2 Nf
-  double* su = cf + 2 * Nf;              // kPP x nc pencil values
-  double* sb = su + kPP * nc;            // kPP x nc scaled coefficients
-  const int tid = threadIdx.x;
-  const int p0 = blockIdx.x * kPP;
-  for (int j = tid; j < 2 * Nc; j += kPT) cc[j] = cospi(double(j) / double(Nc));
-  for (int j = tid; j < 2 * Nf; j += kPT) cf[j] = cospi(double(j) / double(Nf));
-  for (int e = tid; e < kPP * nc; e += kPT) {
-    const int m = e / kPP, pl = e - m * kPP;
-    const int p = p0 + pl;
-    double v = 0.0;
-    if (p < npen) {
-      long long b, st;
-      pencil_geom(axis, p, ns, &b, &st);
-      v = double(src[b + m * st]);
+  const int Rc = Nc / 2 + 1, Rf = Nf / 2 + 1, KS = (Rc + 3) / 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int li = lane & 15, lk = lane >> 4;
+  const int row0 = blockIdx.y * 16 * RB;
+  const int ntasks = (npen + 15) / 16;
+  // the loads of U steps of pairs (j, Nc - j) are in flight at once, those of
+  // the first task behind the tables (rows past Rc read the pencil's first node
+  // and count as zeros)
+  constexpr int U = 8;
+  T lo[U], hi[U];
+  auto load = [&](const T* u, int st, int k0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int x = 0; x < U; ++x) {
+      const int j = 4 * (k0 + x) + lk, jj = j < Rc ? j : 0;
+      lo[x] = u[(size_t)jj * st];
+      hi[x] = u[(size_t)(Nc - jj) * st];
     }
-    su[pl * nc + m] = v;
+  };
+  int task = blockIdx.x * kPW + wave;
+  auto pencil = [&](int t) __attribute__((always_inline)) {
+    const int p = t * 16 + li;
+    return p < npen ? p : npen - 1;
+  };
+  size_t bs;
+  int ss;
+  pencil_geom(axis, pencil(task), ns, &bs, &ss);
+  load(src + bs, ss, 0);
+  // row factors sin(Nc theta_i) sin(theta_i) / Nc and cos(theta_i), column
+  // factors (-1)^j / c_j and cos(phi_j); every angle is an exact fraction in the
+  // first quadrant
+  double* rf = (double*)smem;            // 16 RB x 2
+  double* cf = rf + 32 * RB;           // 4 KS x 2
+  double* tab = cf + 8 * KS;             // fragments [block][even, odd][step][lane]
+  for (int e = tid; e < 16 * RB + 4 * KS; e += 64 * kPW) {
+    if (e < 16 * RB) {
+      const int i = row0 + e < Rf ? row0 + e : Rf - 1;
+      int t = (int)((long long)i * Nc % (2 * Nf));
+      const bool neg = t >= Nf;
+      if (neg) t -= Nf;
+      if (2 * t > Nf) t = Nf - t;
+      const double v = sinpi(double(t) / double(Nf)) * sinpi(double(i) / double(Nf)) / double(Nc);
+      rf[2 * e] = neg ? -v : v;
+      rf[2 * e + 1] = sinpi(double(Nf - 2 * i) / double(2 * Nf));
+    } else {
+      const int j = e - 16 * RB;
+      cf[2 * j] = j == 0 ? 0.5 : 2 * j == Nc ? ((j & 1) ? -0.5 : 0.5) : (j & 1) ? -1.0 : 1.0;
+      cf[2 * j + 1] = j < Rc ? sinpi(double(Nc - 2 * j) / double(2 * Nc)) : 0.0;
+    }
   }
   __syncthreads();
-  // coefficients b_k = X_k / (2 Nc) (k < Nc), b_Nc = X_Nc / (4 Nc) when padding
-  for (int e = tid; e < kPP * nc; e += kPT) {
-    const int pl = e / nc, k = e - pl * nc;
-    const double* u = su + pl * nc;
-    double acc = u[0] + ((k & 1) ? -u[Nc] : u[Nc]);
-    int idx = 0;
-    for (int m = 1; m < Nc; ++m) {
-      idx += k;
-      if (idx >= 2 * Nc) idx -= 2 * Nc;
-      acc += 2.0 * u[m] * cc[idx];
+  // lane l of a fragment: row 16 block + l % 16, column 4 step + l / 16
+  const double inv = 1.0 / (double(Nf) * double(Nc));
+  for (int e = tid; e < RB * KS * 64; e += 64 * kPW) {
+    const int l = e & 63, bk = e >> 6, blk = bk / KS, ks = bk - blk * KS;
+    const int r = 16 * blk + (l & 15), j = 4 * ks + (l >> 4), i = row0 + r;
+    double pe = 0.0, po = 0.0;
+    if (i < Rf && j < Rc) {
+      const int m = i * Nc, q = j * Nf;
+      if (m == q) {
+        pe = 0.5;
+        po = 0.5;
+      } else {
+        const int t = 2 * (m + q) > Nf * Nc ? Nf * Nc - m - q : m + q;
+        const double f = rf[2 * r] * cf[2 * j] / (sinpi(double(t) * inv) * sinpi(double(m - q) * inv));
+        pe = f * ((Nc & 1) ? cf[2 * j + 1] : rf[2 * r + 1]);
+        po = f * ((Nc & 1) ? rf[2 * r + 1] : cf[2 * j + 1]);
+      }
     }
-    double sc = 1.0 / (2.0 * Nc);
-    if (k == Nc && Nf > Nc) sc *= 0.5;
-    if (Nf == Nc && (k == 0 || k == Nc)) sc = 1.0 / (2.0 * Nc);
-    sb[pl * nc + k] = acc * sc;
+    tab[((blk * 2) * KS + ks) * 64 + l] = pe;
+    tab[((blk * 2 + 1) * KS + ks) * 64 + l] = po;
   }
   __syncthreads();
-  // fine values: b_0 + 2 sum_{k=1}^{Nc} b_k cos(pi k m / Nf)  (b_Nf term when Nf == Nc)
-  for (int e = tid; e < kPP * nf; e += kPT) {
-    const int m = e / kPP, pl = e - m * kPP;
-    const int p = p0 + pl;
-    if (p >= npen) continue;
-    const double* b = sb + pl * nc;
-    double acc = b[0];
-    const int kend = (Nf == Nc) ? Nc - 1 : Nc;
-    int idx = 0;
-    for (int k = 1; k <= kend; ++k) {
-      idx += m;
-      if (idx >= 2 * Nf) idx -= 2 * Nf;
-      acc += 2.0 * b[k] * cf[idx];
+  for (; task < ntasks; task += gridDim.x * kPW) {
+    V4 se[RB], so[RB];
+#pragma unroll
+    for (int b = 0; b < RB; ++b) se[b] = so[b] = V4{0, 0, 0, 0};
+    for (int k0 = 0; k0 < KS; k0 += U) {
+      if (k0) load(src + bs, ss, k0);
+#pragma unroll
+      for (int x = 0; x < U; ++x) {
+        if (k0 + x >= KS) break;
+        const bool in = 4 * (k0 + x) + lk < Rc;
+        const double a = in ? double(lo[x]) : 0.0, b = in ? double(hi[x]) : 0.0;
+#pragma unroll
+        for (int q = 0; q < RB; ++q) {
+          se[q] = Mfma<double>::mac(tab[((q * 2) * KS + k0 + x) * 64 + lane], a + b, se[q]);
+          so[q] = Mfma<double>::mac(tab[((q * 2 + 1) * KS + k0 + x) * 64 + lane], a - b, so[q]);
+        }
+      }
     }
-    if (Nf == Nc) acc += ((m & 1) ? -b[Nc] : b[Nc]);
-    long long bd, sd;
-    pencil_geom(axis, p, nd, &bd, &sd);
-    dst[bd + m * sd] = T(acc);
+    size_t bd;
+    int sd;
+    pencil_geom(axis, pencil(task), nd, &bd, &sd);
+    const bool valid = task * 16 + li < npen;
+    const int next = task + gridDim.x * kPW;
+    if (next < ntasks) {
+      pencil_geom(axis, pencil(next), ns, &bs, &ss);
+      load(src + bs, ss, 0);
+    }
+    if (!valid) continue;
+#pragma unroll
+    for (int q = 0; q < RB; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = row0 + 16 * q + Mfma<double>::row(lk, r);
+        if (i >= Rf) continue;
+        dst[bd + (size_t)i * sd] = T(se[q][r] + so[q][r]);
+        if (2 * i != Nf) dst[bd + (size_t)(Nf - i) * sd] = T(se[q][r] - so[q][r]);
+      }
   }
+}
+
+}  // namespace
+
+namespace {
+
+template <typename T, int RB>
+int launch_prolong_axis(const T* in, T* out, int axis, const int* cur, const int* nxt, hipStream_t s) {
+  const int npen = axis == 2 ? cur[0] * cur[1] : axis == 1 ? cur[0] * cur[2] : cur[1] * cur[2];
+  const int lds = prolong_lds_bytes(cur[axis] - 1, RB);
+  if (lds > 64 * 1024)
+    if (int rc = hip_check(hipFuncSetAttribute((const void*)k_prolong_axis<T, RB>,
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, lds),
+                           "prolongation LDS attribute"))
+      return rc;
+  // a workgroup for RB row blocks and a task per wave, up to kPWG in all (each
+  // forms its own tables)
+  const int groups = ((nxt[axis] - 1) / 2 + 16 * RB) / (16 * RB);
+  const int need = (npen + 16 * kPW - 1) / (16 * kPW), most = kPWG / groups > 0 ? kPWG / groups : 1;
+  hipLaunchKernelGGL((k_prolong_axis<T, RB>), dim3(need < most ? need : most, groups), dim3(64 * kPW), lds, s, in, out,
+                     axis, cur[0], cur[1], cur[2], nxt[0], nxt[1], nxt[2]);
+  return hip_check(hipGetLastError(), "prolongation");
 }
 
 }  // namespace
@@ -107,20 +208,20 @@ int prolong_t(const cheb_plan* pc, const cheb_plan* pf, const T* uc, T* uf, T* t
     int nxt[3] = {cur[0], cur[1], cur[2]};
     nxt[axis] = pf->g.n[axis];
     T* out = step == 2 ? uf : (step == 0 ? tmp1 : tmp2);
-    const int npen = axis == 2 ? cur[0] * cur[1] : axis == 1 ? cur[0] * cur[2] : cur[1] * cur[2];
     const int Nc = cur[axis] - 1, Nf = nxt[axis] - 1;
-    const size_t lds = (size_t)(2 * Nc + 2 * Nf + 2 * kPP * (Nc + 1)) * sizeof(double);
-    if (lds > 64 * 1024) {
-      if (hipFuncSetAttribute((const void*)k_prolong_axis<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)lds) != hipSuccess) {
-        (void)hipGetLastError();
-        set_error("prolongation tile needs more LDS than the device grants");
-        return CHEB_ERR_UNSUPPORTED;
-      }
+    // the sizes the call takes: 17 Nc + Nf + 16 <= 10240 (Nc = Nf: 568)
+    if (17 * Nc + Nf + 16 > 10240) {
+      set_error("prolongation: axis too long");
+      return CHEB_ERR_UNSUPPORTED;
     }
-    hipLaunchKernelGGL(k_prolong_axis<T>, dim3((npen + kPP - 1) / kPP), dim3(kPT), lds, s, in, out, axis,
-                       cur[0], cur[1], cur[2], nxt[0], nxt[1], nxt[2]);
-    int rc = hip_check(hipGetLastError(), "prolongation");
+    // three row blocks per workgroup read a pencil fewer times and two form
+    // smaller tables: 257^3, 4129 tasks a pass, takes 185 us with three and
+    // 220 us with two, 181^3, 2048 tasks, 81 and 76 us, 129^3 47 and 41 us
+    const int blocks = (Nf / 2 + 16) / 16;
+    const int npen = axis == 2 ? cur[0] * cur[1] : axis == 1 ? cur[0] * cur[2] : cur[1] * cur[2];
+    const bool three = npen > 16 * 3072 && (blocks + 2) / 3 < (blocks + 1) / 2 && prolong_lds_bytes(Nc, 3) <= 80 * 1024;
+    int rc = three ? launch_prolong_axis<T, 3>(in, out, axis, cur, nxt, s)
+                   : launch_prolong_axis<T, 2>(in, out, axis, cur, nxt, s);
     if (rc) return rc;
     in = out;
     for (int i = 0; i < 3; ++i) cur[i] = nxt[i];

@@ -685,14 +685,20 @@ enum { FDM_XFULL = 1, FDM_YFULL = 2, FDM_SCALE = 4, FDM_MID = 8 };
 // symmetric first):
 //   0  plain: every row block runs the whole k range;
 //   1  the input enters through Q^T: the operand is the pair sums
-//      x_j + x_{m-1-j} (the middle node of odd m kept) for the symmetric row
+//      x_j + x_{m-1-j} (the middle node of odd m twice, its column halved) for the symmetric row
 //      blocks and the differences for the antisymmetric ones;
 //   2  the output leaves through Q: row i of the symmetric blocks is a_i, of
 //      the antisymmetric ones b_i (same lane and register), and node i
 //      receives a_i + b_i, node m-1-i a_i - b_i, the middle node a_p.
-// Kinds 1 and 2 do half the multiply-adds; they need ps = ceil(m/2) to be a
-// multiple of 16, and then ps = MP/2.  The middle pair takes SPLIT 3: kind 1
+// Kinds 1 and 2 do half the multiply-adds.  Each half is padded to whole 16-row
+// blocks, MP = 32 ceil(ps / 16) with ps = ceil(m/2): row r of block rb is the
+// symmetric mode 16 rb + r below MP/2 and the antisymmetric mode ps + (16 rb +
+// r - MP/2) from there on (fdm_mode).  The middle pair takes SPLIT 3: kind 1
 // for the first table, kind 2 for the second (SPLIT 0: both plain).
+// Every centro-symmetric axis takes them.  With the halves left unpadded (only
+// ps = 16, 32, 48, 64 split) m = 119 took 30 steps of 8 row blocks for 16, and
+// FP64 could not hold both tables of a middle pair: an application at 121^3
+// took 126 us and takes 78 us now.
 
 // k-index of MFMA step ks for lane group lk (lane / 16): the row that the
 // accumulator of the same type holds in register ks % 4 of row block ks / 4
@@ -724,8 +730,19 @@ __device__ inline long long face_node(long long u, int n0, int n1, int n2) {
   return ((long long)i * n1 + j) * n2 + k;
 }
 
+// mode held by row `row` of a kind 1 contraction's output (see above), -1: padding
+__host__ __device__ constexpr int fdm_mode(int row, int MP, int m) {
+  const int ps = (m + 1) / 2;
+  return row < MP / 2 ? (row < ps ? row : -1) : (row - MP / 2 < m - ps ? ps + row - MP / 2 : -1);
+}
+
 // fragment-table sizes (elements) of one contraction of padded width MP
 __host__ __device__ constexpr int fdm_tab_elems(int MP, int kind) { return (MP / 16) * (kind ? MP / 8 : MP / 4) * 64; }
+
+// padded width MP of an axis of m interior nodes
+__host__ __device__ constexpr int fdm_width(int m, bool split) {
+  return split ? 32 * (((m + 1) / 2 + 15) / 16) : 16 * ((m + 15) / 16);
+}
 
 constexpr int kFdmWaves = 4;  // waves per workgroup
 
@@ -773,38 +790,28 @@ __device__ __forceinline__ T fdm_scale(T v, double ik, double sc, T lam) {
 
 // acc[rb] (16 rows of row block rb, every rb) = table x B, k-step by k-step
 // (KIND 0: KF steps; kinds 1, 2: KH steps, the symmetric blocks taking one
-// operand, the antisymmetric ones the other).  MASKED: B holds the pencil's
-// raw loads (see k_fdm_wave's load()), turned into operands here, one step at
-// a time, so that each step waits only for its own loads; otherwise B holds
-// the operands themselves (B[ks] and, kinds 1 and 2, B[KH + ks]).
-template <typename T, int KIND, int NB, int KF, int KH, bool MASKED>
+// operand, the antisymmetric ones the other): B[ks] and, kinds 1 and 2, B[KH +
+// ks].  PAIRS (kind 1): B holds x_j and x_{m-1-j}, turned into sums and
+// differences here, one step at a time, so that each step waits only for its
+// own loads.  Nothing is masked: what a padded step reads meets zero columns of
+// the table (the middle node's sum 2 x a halved one), and an invalid lane's
+// column is not stored.
+template <typename T, int KIND, int NB, int KF, int KH, bool PAIRS>
 __device__ __forceinline__ void contract(const T* __restrict__ tab, int lane, const T (&B)[KF],
-                                         typename Mfma<T>::v4 (&acc)[NB], int lk, int m, bool valid) {
+                                         typename Mfma<T>::v4 (&acc)[NB]) {
   constexpr int NKS = KIND ? KH : KF;
-  constexpr bool F32 = sizeof(T) == sizeof(float);
-  const int ps = (m + 1) / 2, ph = m / 2;
 #pragma unroll
   for (int rb = 0; rb < NB; ++rb) acc[rb] = typename Mfma<T>::v4{0, 0, 0, 0};
 #pragma unroll
   for (int ks = 0; ks < NKS; ++ks) {
     // one step's table reads at a time: hoisting more only costs registers
     __builtin_amdgcn_sched_barrier(0);
-    const int j = fdm_kmap(ks, lk, F32);
-    T bs, ba;  // operand of the symmetric (or every) row block, of the antisymmetric ones
-    if constexpr (!MASKED) {
-      bs = B[ks];
-      ba = KIND ? B[KH + ks] : bs;
-    } else if constexpr (KIND == 1) {
-      // pair sums and differences; the middle node of odd m (j = ph) stands alone
-      const T xj = B[ks], xr = B[KH + ks];
-      bs = valid ? (j < ph ? xj + xr : xj) : T(0);
-      ba = valid && j < ph ? xj - xr : T(0);
-    } else if constexpr (KIND == 2) {
-      bs = valid ? B[ks] : T(0);
-      ba = valid && ps + j < m ? B[KH + ks] : T(0);
-    } else {
-      bs = valid && j < m ? B[ks] : T(0);
-      ba = bs;
+    // operand of the symmetric (or every) row block, of the antisymmetric ones
+    T bs = B[ks], ba = KIND ? B[KH + ks] : bs;
+    if constexpr (PAIRS) {
+      const T d = bs - ba;
+      bs = bs + ba;
+      ba = d;
     }
 #pragma unroll
     for (int rb = 0; rb < NB; ++rb)
@@ -845,7 +852,7 @@ __global__ __launch_bounds__(64 * kFdmWaves) void k_fdm_wave(FdmArgs g) {
   const int ppb = bsz / m;  // pencils per block
   const int npen = ppb * g.nb;
   const int ntasks = (npen + 15) / 16;
-  const int ps = (m + 1) / 2, ph = m / 2;  // symmetric / antisymmetric halves (split kinds: ps = MP/2)
+  const int ps = (m + 1) / 2, ph = m / 2;  // symmetric / antisymmetric halves
 
   // this lane's pencil of a task: its first element in X and Y, and (scaling)
   // the block's 1 / Kc and the pencil's indices across the axis
@@ -882,14 +889,14 @@ __global__ __launch_bounds__(64 * kFdmWaves) void k_fdm_wave(FdmArgs g) {
   // kind 2: the first ps rows, then the rest).  Every load is issued, rows past
   // the pencil clamped to its last node and invalid lanes reading element 0, so
   // the number in flight is static and the matrix-core steps wait only for
-  // their own loads; contract() masks the values it does not use.
+  // their own loads.
   T B[KF];
   auto load = [&]() {
     if (SA == 1) {
 #pragma unroll
       for (int ks = 0; ks < KH; ++ks) {
-        const int j = fdm_kmap(ks, lk, F32);  // < ps
-        const int jr = j < ph ? m - 1 - j : j;
+        const int j = min(fdm_kmap(ks, lk, F32), ps - 1);
+        const int jr = m - 1 - j;  // the middle node is its own mirror
         B[ks] = X[bx + (long long)j * sxa];
         B[KH + ks] = X[bx + (long long)jr * sxa];
       }
@@ -898,7 +905,7 @@ __global__ __launch_bounds__(64 * kFdmWaves) void k_fdm_wave(FdmArgs g) {
       for (int ks = 0; ks < KH; ++ks) {
         const int j = fdm_kmap(ks, lk, F32);
         const int j2 = ps + j < m ? ps + j : m - 1;
-        B[ks] = X[bx + (long long)j * sxa];
+        B[ks] = X[bx + (long long)min(j, ps - 1) * sxa];
         B[KH + ks] = X[bx + (long long)j2 * sxa];
       }
     } else {
@@ -948,7 +955,7 @@ __global__ __launch_bounds__(64 * kFdmWaves) void k_fdm_wave(FdmArgs g) {
     // every row block at once, k-step by k-step: eight independent
     // accumulation chains, started as soon as the first rows arrive
     V4 acc[NB];
-    contract<T, SA, NB, KF, KH, true>(tabA, lane, B, acc, lk, m, valid);
+    contract<T, SA, NB, KF, KH, SA == 1>(tabA, lane, B, acc);
     if constexpr (MID) {
       // the first contraction, scaled, is the second one's B operand
       const int a0 = axis == 0 ? 1 : 0, a1 = axis == 2 ? 1 : 2;
@@ -958,10 +965,11 @@ __global__ __launch_bounds__(64 * kFdmWaves) void k_fdm_wave(FdmArgs g) {
       for (int rb = 0; rb < NB; ++rb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int i = 16 * rb + Mfma<T>::row(lk, r);
-          B[4 * rb + r] = i < m ? fdm_scale<T>(acc[rb][r], ik, sc, lam_s[axis * 128 + i]) : T(0);
+          const int row = 16 * rb + Mfma<T>::row(lk, r);
+          const int i = SA ? fdm_mode(row, MP, m) : row < m ? row : -1;
+          B[4 * rb + r] = i >= 0 ? fdm_scale<T>(acc[rb][r], ik, sc, lam_s[axis * 128 + i]) : T(0);
         }
-      contract<T, SB, NB, KF, KH, false>(tabB, lane, B, acc, lk, m, valid);
+      contract<T, SB, NB, KF, KH, false>(tabB, lane, B, acc);
     } else if constexpr (SCL) {
       const int a0 = axis == 0 ? 1 : 0, a1 = axis == 2 ? 1 : 2;
       const double sc = valid ? double(lam_s[a0 * 128 + ia]) + double(lam_s[a1 * 128 + ib]) : 0.0;
@@ -970,8 +978,9 @@ __global__ __launch_bounds__(64 * kFdmWaves) void k_fdm_wave(FdmArgs g) {
       for (int rb = 0; rb < NB; ++rb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int i = 16 * rb + Mfma<T>::row(lk, r);
-          if (i < m) acc[rb][r] = fdm_scale<T>(acc[rb][r], ik, sc, lam_s[axis * 128 + i]);
+          const int row = 16 * rb + Mfma<T>::row(lk, r);
+          const int i = SA == 1 ? fdm_mode(row, MP, m) : row < m ? row : -1;
+          if (i >= 0) acc[rb][r] = fdm_scale<T>(acc[rb][r], ik, sc, lam_s[axis * 128 + i]);
         }
     }
     constexpr int SOUT = MID ? SB : SA;  // the kind whose outputs are stored
@@ -996,8 +1005,9 @@ __global__ __launch_bounds__(64 * kFdmWaves) void k_fdm_wave(FdmArgs g) {
         for (int rb = 0; rb < NB; ++rb)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            const int i = 16 * rb + Mfma<T>::row(lk, r);
-            if (i < m) Y[by + (long long)i * sya] = acc[rb][r];
+            const int row = 16 * rb + Mfma<T>::row(lk, r);
+            const int i = SOUT == 1 ? fdm_mode(row, MP, m) : row < m ? row : -1;
+            if (i >= 0) Y[by + (long long)i * sya] = acc[rb][r];
           }
       }
     }
@@ -1118,17 +1128,19 @@ static void fdm_table(const double* M, int m, int mp, int kind, bool tr, bool f3
     for (int ks = 0; ks < nks; ++ks)
       for (int lane = 0; lane < 64; ++lane) {
         const int row = 16 * rb + (lane & 15), k = fdm_kmap(ks, lane >> 4, f32);
-        const bool anti = kind != 0 && 16 * rb >= ps;
+        const bool anti = kind != 0 && 2 * rb >= nbk;
         int r = row, col = k;
         bool ok = row < m && k < m;
         if (kind == 1) {
-          ok = row < m && k < (anti ? ph : ps);
+          r = fdm_mode(row, mp, m);
+          ok = r >= 0 && k < (anti ? ph : ps);
         } else if (kind == 2) {
-          r = anti ? row - ps : row;
+          r = anti ? row - mp / 2 : row;
           col = anti ? ps + k : k;
           ok = r < (anti ? ph : ps) && k < (anti ? ph : ps);
         }
-        out[((size_t)rb * nks + ks) * 64 + lane] = ok ? (tr ? M[(size_t)col * m + r] : M[(size_t)r * m + col]) : 0.0;
+        const double v = ok ? (tr ? M[(size_t)col * m + r] : M[(size_t)r * m + col]) : 0.0;
+        out[((size_t)rb * nks + ks) * 64 + lane] = kind == 1 && col == m - 1 - col ? 0.5 * v : v;
       }
 }
 
@@ -1179,12 +1191,10 @@ int precond_setup(cheb_plan* p) {
     const std::vector<double>& V = Vv[src[a]];
     const std::vector<double>& Vi = Viv[src[a]];
     ax[a].m = m;
-    // the even-odd contraction needs the centro-symmetric factors and whole
-    // 16-row halves
     const int sa = src[a];
     const bool centro_a = p->g.bc[2 * sa] == p->g.bc[2 * sa + 1] && face_sigma(p, 2 * sa) == face_sigma(p, 2 * sa + 1);
-    ax[a].split = centro_a && m <= 128 && ((m + 1) / 2) % 16 == 0 ? 1 : 0;
     ax[a].centro = centro_a ? 1 : 0;
+    ax[a].split = centro_a && m <= 128 ? 1 : 0;
     ax[a].off_V = off64;
     host.insert(host.end(), V.begin(), V.end());
     off64 += (size_t)m * m;
@@ -1212,7 +1222,7 @@ int precond_setup(cheb_plan* p) {
         for (int tr = 0; tr < 2; ++tr) ax[a].off_tab[dir][tr] = ax[src[a]].off_tab[dir][tr];
       continue;
     }
-    const int mp = 16 * ((m + 15) / 16);
+    const int mp = fdm_width(m, ax[a].split);
     for (int dir = 0; dir < 2; ++dir)
       for (int tr = 0; tr < 2; ++tr) {
         off64 = (off64 + 3) / 4 * 4;  // 16-byte aligned in both precisions
@@ -1226,7 +1236,7 @@ int precond_setup(cheb_plan* p) {
   std::vector<float> host32(host.size());
   for (size_t i = 0; i < host.size(); ++i) host32[i] = float(host[i]);
   for (const TabJob& j : jobs) {
-    const int m = ax[j.a].m, mp = 16 * ((m + 15) / 16);
+    const int m = ax[j.a].m, mp = fdm_width(m, j.kind != 0);
     // the V^{-1} side applies V^{-1} (V^T when transposed), the V side V (V^{-1} T)
     const double* M = host.data() + ((j.dir == 0) != (j.tr != 0) ? ax[j.a].off_Vi : ax[j.a].off_V);
     std::vector<double> t(fdm_tab_elems(mp, j.kind));
@@ -1291,12 +1301,11 @@ static int launch_fdm(const FdmArgs& f, hipStream_t s) {
 template <typename T, int MODE, int SPLIT>
 static int launch_fdm_mode(const FdmArgs& f, hipStream_t s) {
   if constexpr (SPLIT != 0) {
-    // only the widths whose halves are whole 16-row blocks
-    switch ((f.m + 15) / 16) {
-      case 2: return launch_fdm<T, 32, MODE, SPLIT>(f, s);
-      case 4: return launch_fdm<T, 64, MODE, SPLIT>(f, s);
-      case 6: return launch_fdm<T, 96, MODE, SPLIT>(f, s);
-      case 8: return launch_fdm<T, 128, MODE, SPLIT>(f, s);
+    switch (fdm_width(f.m, true)) {
+      case 32: return launch_fdm<T, 32, MODE, SPLIT>(f, s);
+      case 64: return launch_fdm<T, 64, MODE, SPLIT>(f, s);
+      case 96: return launch_fdm<T, 96, MODE, SPLIT>(f, s);
+      case 128: return launch_fdm<T, 128, MODE, SPLIT>(f, s);
       default: set_error("even-odd contraction: unsupported width"); return CHEB_ERR_INVALID_ARG;
     }
   } else {

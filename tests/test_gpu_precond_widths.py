@@ -1,0 +1,62 @@
+"""The preconditioner's contractions at the interior sizes where their padding
+can go wrong: halves of one to four 16-row blocks and their remainders, with and
+without a middle node, next to axes that are not mirror-symmetric, for both
+types and the transpose, against the Kronecker inverse of the 1-D operators."""
+import numpy as np
+import pytest
+
+from oracle import cheb_oracle as O
+from tests.gpu_util import log, require_gpu, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+KC = 1.7
+EDGE = (1.0, 2.0, 1.5)
+
+
+def along(M, x, axis):
+    return np.moveaxis(np.tensordot(M, x, (1, axis)), 0, axis)
+
+
+@pytest.mark.parametrize("shape,bc", [
+    ((3, 4, 5), (0, 0, 1, 1, 0, 0)),          # interior 1, 2, 3
+    ((33, 34, 35), (0, 0, 1, 1, 0, 0)),       # 31, 32, 33: one whole half, one row past it
+    ((36, 49, 12), (1, 0, 0, 0, 0, 0)),       # 34, 47, 10; x not mirror-symmetric
+    ((20, 67, 100), (0, 0, 0, 0, 1, 1)),      # 18, 65, 98
+    ((67, 41, 66), (0, 0, 0, 1, 0, 0)),       # 65, 39, 64; y not mirror-symmetric
+    ((12, 100, 66), (0, 0, 0, 1, 1, 1)),      # 10, 98, 64; y not, and wide
+    ((9, 70, 99), (1, 1, 1, 1, 0, 1)),        # 7, 68, 97; z not
+    ((10, 66, 52), (0, 1, 1, 0, 0, 1)),       # 8, 64, 50; none
+    ((5, 130, 130), (0, 0, 0, 0, 0, 0)),      # 3, 128, 128
+    ((6, 129, 122), (0, 0, 1, 1, 0, 0)),      # 4, 127, 120
+])
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+def test_precond_widths(shape, bc, prec):
+    require_gpu()
+    import torch
+    from paper_2606_21410_amd.api import Plan
+    dt = torch.float64 if prec == "f64" else torch.float32
+    plan = Plan(shape, (0.0, 0.0, 0.0), EDGE, bc, prec)
+    r = np.random.default_rng(sum(shape)).standard_normal(shape)
+    r = r.astype(np.float64 if prec == "f64" else np.float32)
+    A = [O.reduced_1d(O.diff_matrix(shape[a] - 1, 0.0, EDGE[a]), bc[2 * a], bc[2 * a + 1]) for a in range(3)]
+    lam, V = zip(*(np.linalg.eig(M) for M in A))
+    lam, V = [x.real for x in lam], [x.real for x in V]
+    Vi = [np.linalg.inv(x) for x in V]
+    den = KC * (lam[0][:, None, None] + lam[1][None, :, None] + lam[2][None, None, :])
+    # rounding of the six contractions in the type's tables, and (in FP64) of the
+    # decomposition, whose error in an eigenvalue is that of the matrix
+    eps = 2.0 ** -53 if prec == "f64" else 2.0 ** -24
+    tol = eps * sum(len(x) * np.linalg.cond(x) for x in V) + 2.0 ** -53 * 4 * sum(np.linalg.cond(M) for M in A)
+    for tr in (False, True):
+        log(f"precond {prec} {shape} {bc} transpose={tr}")
+        got = to_host(plan.precond(to_dev(r, dt), KC, transpose=tr))
+        x = r[1:-1, 1:-1, 1:-1].astype(np.float64)
+        for a in range(3):
+            x = along(V[a].T if tr else Vi[a], x, a)
+        x = x / den
+        for a in range(3):
+            x = along(Vi[a].T if tr else V[a], x, a)
+        assert np.linalg.norm(got[1:-1, 1:-1, 1:-1] - x) <= tol * np.linalg.norm(x)
+        got[1:-1, 1:-1, 1:-1] = 0
+        assert not got.any()

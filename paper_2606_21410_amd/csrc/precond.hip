@@ -16,11 +16,12 @@
 // back-substitution for the eigenvectors), and the inverse by Gauss-Jordan.
 // An axis with the same face type at both ends has a centro-symmetric 1-D
 // operator, which splits into two half-size problems.
-// Apply (device): pack interior -> three dense axis contractions with V^{-1}
-// -> divide by the eigenvalue sums -> three contractions with V -> unpack (for
-// m <= 128 the packing, scaling and unpacking run inside the contractions).
-// The contractions run on the matrix cores (MFMA 16x16x4): a pencil-tile kernel
-// for m <= 128, a generic strided batched GEMM beyond.
+// Apply (device): V^{-1} along z, y and x, division by the eigenvalue sums, V
+// along x, y and z, all on the matrix cores (MFMA 16x16x4).  Every axis with m <=
+// 128: three launches, the packing and unpacking inside them -- z and y of one
+// x-plane in LDS (fdm_plane.h), x in and out with the scaling between
+// (k_fdm_mid), y and z again; planes that do not fit take an axis at a time
+// (k_fdm_wave).  Longer axes: packed blocks through a strided batched GEMM.
 #include <algorithm>
 #include <cmath>
 #include <thread>
@@ -28,9 +29,19 @@
 
 #include "cheb_host.h"
 #include "dev_common.h"
+#include "fdm_plane.h"
 #include "internal.h"
 
 namespace cheb {
+
+PLANE_EXTERN(double, 1);
+PLANE_EXTERN(double, 2);
+PLANE_EXTERN(double, 3);
+PLANE_EXTERN(double, 4);
+PLANE_EXTERN(float, 1);
+PLANE_EXTERN(float, 2);
+PLANE_EXTERN(float, 3);
+PLANE_EXTERN(float, 4);
 
 // ---------------------------------------------------------------------------
 // host linear algebra
@@ -693,18 +704,12 @@ enum { FDM_XFULL = 1, FDM_YFULL = 2, FDM_SCALE = 4, FDM_MID = 8 };
 // Kinds 1 and 2 do half the multiply-adds.  Each half is padded to whole 16-row
 // blocks, MP = 32 ceil(ps / 16) with ps = ceil(m/2): row r of block rb is the
 // symmetric mode 16 rb + r below MP/2 and the antisymmetric mode ps + (16 rb +
-// r - MP/2) from there on (fdm_mode).  The middle pair takes SPLIT 3: kind 1
-// for the first table, kind 2 for the second (SPLIT 0: both plain).
+// r - MP/2) from there on (fdm_mode).  The middle pair of a split axis runs in
+// k_fdm_mid, kind 1 then kind 2.
 // Every centro-symmetric axis takes them.  With the halves left unpadded (only
 // ps = 16, 32, 48, 64 split) m = 119 took 30 steps of 8 row blocks for 16, and
 // FP64 could not hold both tables of a middle pair: an application at 121^3
 // took 126 us and takes 78 us now.
-
-// k-index of MFMA step ks for lane group lk (lane / 16): the row that the
-// accumulator of the same type holds in register ks % 4 of row block ks / 4
-__host__ __device__ constexpr int fdm_kmap(int ks, int lk, bool f32) {
-  return f32 ? 16 * (ks / 4) + 4 * lk + (ks % 4) : 4 * ks + lk;
-}
 
 // linear offset of boundary node u of an n0 x n1 x n2 field (faces x, y, z)
 __device__ inline long long face_node(long long u, int n0, int n1, int n2) {
@@ -748,9 +753,7 @@ constexpr int kFdmWaves = 4;  // waves per workgroup
 
 template <typename T>
 __host__ __device__ constexpr int fdm_lds_bytes(int MP, int MODE, int SPLIT) {
-  const bool mid = MODE & FDM_MID;
-  const int ka = mid ? (SPLIT ? 1 : 0) : SPLIT, kb = mid ? (SPLIT ? 2 : 0) : 0;
-  return (fdm_tab_elems(MP, ka) + (mid ? fdm_tab_elems(MP, kb) : 0) + ((MODE & FDM_SCALE) ? 3 * 128 : 0)) *
+  return (((MODE & FDM_MID) ? 2 : 1) * fdm_tab_elems(MP, SPLIT) + ((MODE & FDM_SCALE) ? 3 * 128 : 0)) *
          (int)sizeof(T);
 }
 
@@ -819,6 +822,203 @@ __device__ __forceinline__ void contract(const T* __restrict__ tab, int lane, co
   }
 }
 
+// The same quotient with the reciprocal taken ahead of the value: FP64 corrects
+// the product once, which leaves it within an ulp's rounding of the division
+// (measured over the whole preconditioner: the same errors to two digits).
+template <typename T>
+__device__ __forceinline__ T fdm_rcp(double sc, T lam) {
+  if constexpr (sizeof(T) == sizeof(float)) return __builtin_amdgcn_rcpf(float(sc) + lam);
+  else return 1.0 / (sc + lam);
+}
+template <typename T>
+__device__ __forceinline__ T fdm_scale_rcp(T v, double ik, double sc, T lam, T rc) {
+  if constexpr (sizeof(T) == sizeof(float)) {
+    return v * float(ik) * rc;
+  } else {
+    const double n = v * ik, q = n * rc;
+    return fma(fma(-(sc + lam), q, n), rc, q);
+  }
+}
+
+// The middle pair of an even-odd split axis: modes, scaling and nodes again of
+// packed pencils, two waves to a task of 16 pencils, one per parity.  Each
+// parity's modes pass through both contractions on their own -- the symmetric
+// wave contracts the pair sums, scales, and contracts back to a_i, the
+// antisymmetric one the differences to b_i -- and only the node values a_i +- b_i
+// need both, which the waves exchange through LDS, half of the row blocks each
+// way (a_i and b_i sit in the same lane and register).  Eight waves, two to a
+// SIMD: one's matrix instructions cover the other's table reads (a wave to a
+// task with all the row blocks, the split before this one, left the SIMD to one
+// wave); the reciprocals of the eigenvalue sums are formed beside the first
+// contraction's steps.  Both tables come first: fetching the second one beside
+// the first contraction costs registers that FP64 does not have (16 spilled, 24.7
+// us).  129^3: 22.0 us in FP64 (23.3 with a wave to a task), 13.7 in FP32.
+constexpr int kMidWaves = 8;
+
+template <typename T, int RB>
+__host__ __device__ constexpr int fdm_mid_lds() {
+  return (2 * fdm_tab_elems(32 * RB, 1) + 3 * 128 + kMidWaves * 4 * 64) * (int)sizeof(T);
+}
+
+template <typename T, int RB>
+__global__ __launch_bounds__(64 * kMidWaves) void k_fdm_mid(FdmArgs g) {
+  if (g.gate && !*g.gate) return;
+  constexpr int KS = 4 * RB, TAB = fdm_tab_elems(32 * RB, 1), NT = 64 * kMidWaves;
+  constexpr int HO = (RB + 1) / 2;  // row blocks whose nodes the symmetric wave stores
+  constexpr bool F32 = sizeof(T) == sizeof(float);
+  typedef typename Mfma<T>::v4 V4;
+  typedef int I4 __attribute__((ext_vector_type(4)));
+  extern __shared__ __align__(16) unsigned char smem[];
+  T* tabA = (T*)smem;
+  T* tabB = tabA + TAB;
+  T* lam_s = tabB + TAB;
+  T* xch = lam_s + 3 * 128;  // one row block per wave
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), par = wave & 1;
+  const int li = lane & 15, lk = lane >> 4;
+  const int m = g.m, axis = g.axis, ps = (m + 1) / 2, ph = m / 2, mine = par ? ph : ps;
+  const T* X = (const T*)g.X;
+  T* Y = (T*)g.Y;
+  const int plane = g.m1 * g.m2, bsz = plane * g.m0;
+  const int st0 = axis == 2 ? 1 : axis == 1 ? g.m2 : plane;
+  const int ppb = bsz / m, npen = ppb * g.nb, ntasks = (npen + 15) / 16;
+  bool valid = false;
+  long long bx = 0;
+  int ia = 0, ib = 0, bi = 0;
+  auto locate = [&](int task) __attribute__((always_inline)) {
+    const int q = task * 16 + li;
+    valid = q < npen;
+    if (!valid) return;
+    bi = q / ppb;
+    const int qq = q - bi * ppb;
+    // the pencil's indices across the axis
+    const int w = axis == 2 ? g.m1 : g.m2;
+    ia = qq / w;
+    ib = qq - ia * w;
+    bx = (long long)bi * bsz + (axis == 0 ? (long long)qq : axis == 1 ? (long long)ia * plane + ib : (long long)qq * g.m2);
+  };
+  T xl[KS], xh[KS];
+  // (the stride is renewed for every use, or the offsets of all the rows stay in
+  // registers across the task loop)
+  auto load = [&]() __attribute__((always_inline)) {
+    int st = st0;
+    asm volatile("" : "+s"(st));
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const int j = min(fdm_kmap(ks, lk, F32), ps - 1);
+      xl[ks] = X[bx + (long long)j * st];
+      xh[ks] = X[bx + (long long)(m - 1 - j) * st];
+    }
+  };
+  constexpr int W = TAB * (int)sizeof(T) / 16, PER = (W + NT - 1) / NT;
+  I4 v[PER];
+  auto fetch = [&](const void* src) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) v[i] = ((const I4*)src)[tid + i * NT < W ? tid + i * NT : W - 1];
+  };
+  auto put = [&](T* dst) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      if (tid + i * NT < W) ((I4*)dst)[tid + i * NT] = v[i];
+  };
+  auto barrier = [&]() __attribute__((always_inline)) {  // over LDS only
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+  };
+  fetch(g.tab);
+  {
+    const T* lp[3] = {(const T*)g.lam0, (const T*)g.lam1, (const T*)g.lam2};
+    const int md[3] = {g.m0, g.m1, g.m2};
+    if (tid < 3 * 128) {
+      const int a = tid >> 7, i = tid & 127;
+      lam_s[tid] = i < md[a] ? lp[a][i] : T(0);
+    }
+  }
+  put(tabA);
+  fetch(g.tab2);
+  put(tabB);
+  int base = blockIdx.x * (kMidWaves / 2);
+  const int task0 = base + (wave >> 1);
+  if (task0 < ntasks) {
+    locate(task0);
+    load();
+  }
+  barrier();
+  const int a0 = axis == 0 ? 1 : 0, a1 = axis == 2 ? 1 : 2;
+  const T* tA = tabA + par * RB * KS * 64 + lane;
+  const T* tB = tabB + par * RB * KS * 64 + lane;
+  for (; base < ntasks; base += gridDim.x * (kMidWaves / 2)) {
+    V4 acc[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) acc[rb] = V4{0, 0, 0, 0};
+    const double sc = valid ? double(lam_s[a0 * 128 + ia]) + double(lam_s[a1 * 128 + ib]) : 1.0;
+    const double ik = valid ? (g.sys ? 1.0 / g.kc[g.sys[bi]] : g.inv_k) : 0.0;
+    // (past the modes of this parity the eigenvalues read are any; they meet zeros)
+    const T* lam = lam_s + axis * 128 + (par ? ps : 0) + Mfma<T>::row(lk, 0);
+    T q[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      __builtin_amdgcn_sched_barrier(0);
+      const T x = par ? xl[ks] - xh[ks] : xl[ks] + xh[ks];
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) acc[rb] = Mfma<T>::mac(tA[(rb * KS + ks) * 64], x, acc[rb]);
+      // register ks % 4 of row block ks / 4
+      q[ks] = fdm_rcp<T>(sc, lam[16 * (ks / 4) + Mfma<T>::row(0, ks % 4)]);
+    }
+    T B[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const int i = 16 * (ks / 4) + Mfma<T>::row(lk, ks % 4);
+      const T l = lam[16 * (ks / 4) + Mfma<T>::row(0, ks % 4)];
+      B[ks] = i < mine ? fdm_scale_rcp<T>(acc[ks / 4][ks % 4], ik, sc, l, q[ks]) : T(0);
+    }
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) acc[rb] = V4{0, 0, 0, 0};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) acc[rb] = Mfma<T>::mac(tB[(rb * KS + ks) * 64], B[ks], acc[rb]);
+    }
+    // the other parity's values of the blocks this wave stores, a block a round
+    int st = st0;
+    asm volatile("" : "+s"(st));
+#pragma unroll
+    for (int r0 = 0; r0 < HO; ++r0) {
+      const bool give = par ? true : HO + r0 < RB;
+      T* out = xch + wave * 256 + lane;
+      const T* in = xch + (wave ^ 1) * 256 + lane;
+      if (give)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const V4 s4 = acc[r0], o4 = acc[HO + r0 < RB ? HO + r0 : r0];
+          out[r * 64] = par ? s4[r] : o4[r];
+        }
+      barrier();
+      const bool take = par ? HO + r0 < RB : true;
+      if (take && valid) {
+        const int blk = par ? HO + r0 : r0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const V4 s4 = acc[r0], o4 = acc[HO + r0 < RB ? HO + r0 : r0];
+          const T other = in[r * 64];
+          const T a = par ? other : s4[r], b = par ? o4[r] : other;
+          const int i = 16 * blk + Mfma<T>::row(lk, r);
+          if (i < ps) Y[bx + (long long)i * st] = a + b;  // the middle node: b is 0
+          if (i < ph) Y[bx + (long long)(m - 1 - i) * st] = a - b;
+        }
+      }
+      barrier();
+    }
+    const int next = base + gridDim.x * (kMidWaves / 2) + (wave >> 1);
+    valid = false;
+    if (next < ntasks) {
+      locate(next);
+      load();
+    }
+  }
+}
+
 template <typename T, int MP, int MODE, int SPLIT>
 __global__ __launch_bounds__(64 * kFdmWaves) void k_fdm_wave(FdmArgs g) {
   if (g.gate && !*g.gate) return;
@@ -826,12 +1026,10 @@ __global__ __launch_bounds__(64 * kFdmWaves) void k_fdm_wave(FdmArgs g) {
   constexpr bool F32 = sizeof(T) == sizeof(float);
   constexpr bool XF = MODE & FDM_XFULL, YF = MODE & FDM_YFULL, SCL = MODE & FDM_SCALE, MID = MODE & FDM_MID;
   constexpr bool FULL = XF || YF;
-  constexpr int SA = MID ? (SPLIT ? 1 : 0) : SPLIT;  // kind of the first (or only) contraction
-  constexpr int SB = MID ? (SPLIT ? 2 : 0) : 0;      // kind of the second one
-  constexpr int TA = fdm_tab_elems(MP, SA), TB = MID ? fdm_tab_elems(MP, SB) : 0;
+  constexpr int SA = SPLIT;
+  constexpr int TA = fdm_tab_elems(MP, SA), TB = MID ? TA : 0;
   static_assert(!MID || SCL, "the middle pair scales between its contractions");
-  static_assert(!MID || SPLIT == 0 || SPLIT == 3, "middle pair: SPLIT 0 or 3");
-  static_assert(MID || SPLIT <= 2, "SPLIT 3 is the middle pair's");
+  static_assert(!MID || SPLIT == 0, "k_fdm_mid is a split axis' middle pair");
   static_assert(SPLIT == 0 || MP >= 32, "split contractions need two row blocks");
   typedef typename Mfma<T>::v4 V4;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -966,10 +1164,9 @@ __global__ __launch_bounds__(64 * kFdmWaves) void k_fdm_wave(FdmArgs g) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int row = 16 * rb + Mfma<T>::row(lk, r);
-          const int i = SA ? fdm_mode(row, MP, m) : row < m ? row : -1;
-          B[4 * rb + r] = i >= 0 ? fdm_scale<T>(acc[rb][r], ik, sc, lam_s[axis * 128 + i]) : T(0);
+          B[4 * rb + r] = row < m ? fdm_scale<T>(acc[rb][r], ik, sc, lam_s[axis * 128 + row]) : T(0);
         }
-      contract<T, SB, NB, KF, KH, false>(tabB, lane, B, acc);
+      contract<T, 0, NB, KF, KH, false>(tabB, lane, B, acc);
     } else if constexpr (SCL) {
       const int a0 = axis == 0 ? 1 : 0, a1 = axis == 2 ? 1 : 2;
       const double sc = valid ? double(lam_s[a0 * 128 + ia]) + double(lam_s[a1 * 128 + ib]) : 0.0;
@@ -983,9 +1180,8 @@ __global__ __launch_bounds__(64 * kFdmWaves) void k_fdm_wave(FdmArgs g) {
           if (i >= 0) acc[rb][r] = fdm_scale<T>(acc[rb][r], ik, sc, lam_s[axis * 128 + i]);
         }
     }
-    constexpr int SOUT = MID ? SB : SA;  // the kind whose outputs are stored
     if (valid) {
-      if constexpr (SOUT == 2) {
+      if constexpr (SA == 2) {
         // rows i of the symmetric blocks hold a_i, of the antisymmetric ones b_i
 #pragma unroll
         for (int rb = 0; rb < NB / 2; ++rb)
@@ -1006,7 +1202,7 @@ __global__ __launch_bounds__(64 * kFdmWaves) void k_fdm_wave(FdmArgs g) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const int row = 16 * rb + Mfma<T>::row(lk, r);
-            const int i = SOUT == 1 ? fdm_mode(row, MP, m) : row < m ? row : -1;
+            const int i = SA == 1 ? fdm_mode(row, MP, m) : row < m ? row : -1;
             if (i >= 0) Y[by + (long long)i * sya] = acc[rb][r];
           }
       }
@@ -1266,36 +1462,54 @@ const double* pc_base<double>(const cheb_plan* p) { return p->pc64; }
 template <>
 const float* pc_base<float>(const cheb_plan* p) { return p->pc32; }
 
-// persistent launch: at most as many workgroups as the device holds at once
-// (queried once per instantiation and device), no more than the tasks need
+// workgroups of `threads` threads the device holds at once (queried once per
+// kernel and device, with the LDS attribute set)
+static int fdm_resident(const void* kern, int threads, int lds, DeviceCache& cache, int* resident) {
+  int dev = 0;
+  if (int rc = current_device(&dev)) return rc;
+  *resident = cache.v[dev].load(std::memory_order_relaxed);
+  if (*resident != 0) return CHEB_OK;
+  int cus = 0, per_cu = 0, rc = CHEB_OK;
+  if (lds > 64 * 1024)
+    rc = hip_check(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds),
+                   "contraction LDS attribute");
+  if (!rc) rc = hip_check(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), "CU count");
+  if (!rc) rc = hip_check(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads, lds), "occupancy query");
+  if (rc) return rc;
+  *resident = (cus > 0 ? cus : 1) * (per_cu > 0 ? per_cu : 1);
+  cache.v[dev].store(*resident, std::memory_order_relaxed);
+  return CHEB_OK;
+}
+
+// persistent launches: at most as many workgroups as the device holds at once, no
+// more than the tasks need
+static int fdm_grid(const FdmArgs& f, int tasks_per_wg, int resident) {
+  const long long npen = (long long)f.m0 * f.m1 * f.m2 / f.m * f.nb;
+  const long long wgs = ((npen + 15) / 16 + tasks_per_wg - 1) / tasks_per_wg;
+  return (int)(wgs < resident ? (wgs > 0 ? wgs : 1) : resident);
+}
+
 template <typename T, int MP, int MODE, int SPLIT>
 static int launch_fdm(const FdmArgs& f, hipStream_t s) {
   constexpr int lds = fdm_lds_bytes<T>(MP, MODE, SPLIT);
   static_assert(lds <= 160 * 1024, "contraction tables exceed LDS");
   static DeviceCache cache;
-  int dev = 0;
-  if (int rc = current_device(&dev)) return rc;
-  int resident = cache.v[dev].load(std::memory_order_relaxed);
-  if (resident == 0) {
-    int cus = 0, per_cu = 0, rc = CHEB_OK;
-    if (lds > 64 * 1024)
-      rc = hip_check(hipFuncSetAttribute((const void*)k_fdm_wave<T, MP, MODE, SPLIT>,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, lds),
-                     "contraction LDS attribute");
-    if (!rc) rc = hip_check(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), "CU count");
-    if (!rc)
-      rc = hip_check(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)k_fdm_wave<T, MP, MODE, SPLIT>,
-                                                                  64 * kFdmWaves, lds),
-                     "occupancy query");
-    if (rc) return rc;
-    resident = (cus > 0 ? cus : 1) * (per_cu > 0 ? per_cu : 1);
-    cache.v[dev].store(resident, std::memory_order_relaxed);
-  }
-  const long long npen = (long long)f.m0 * f.m1 * f.m2 / f.m * f.nb;
-  const long long wgs = ((npen + 15) / 16 + kFdmWaves - 1) / kFdmWaves;
-  const int grid = (int)(wgs < resident ? (wgs > 0 ? wgs : 1) : resident);
-  hipLaunchKernelGGL((k_fdm_wave<T, MP, MODE, SPLIT>), dim3(grid), dim3(64 * kFdmWaves), lds, s, f);
+  int resident = 0;
+  if (int rc = fdm_resident((const void*)k_fdm_wave<T, MP, MODE, SPLIT>, 64 * kFdmWaves, lds, cache, &resident)) return rc;
+  hipLaunchKernelGGL((k_fdm_wave<T, MP, MODE, SPLIT>), dim3(fdm_grid(f, kFdmWaves, resident)), dim3(64 * kFdmWaves), lds,
+                     s, f);
   return hip_check(hipGetLastError(), "axis contraction");
+}
+
+template <typename T, int RB>
+static int launch_fdm_mid(const FdmArgs& f, hipStream_t s) {
+  constexpr int lds = fdm_mid_lds<T, RB>();
+  static_assert(lds <= 160 * 1024, "middle pair's tables exceed LDS");
+  static DeviceCache cache;
+  int resident = 0;
+  if (int rc = fdm_resident((const void*)k_fdm_mid<T, RB>, 64 * kMidWaves, lds, cache, &resident)) return rc;
+  hipLaunchKernelGGL((k_fdm_mid<T, RB>), dim3(fdm_grid(f, kMidWaves / 2, resident)), dim3(64 * kMidWaves), lds, s, f);
+  return hip_check(hipGetLastError(), "middle pair");
 }
 
 template <typename T, int MODE, int SPLIT>
@@ -1316,21 +1530,31 @@ static int launch_fdm_mode(const FdmArgs& f, hipStream_t s) {
       case 4: return launch_fdm<T, 64, MODE, 0>(f, s);
       case 5: return launch_fdm<T, 80, MODE, 0>(f, s);
       case 6: return launch_fdm<T, 96, MODE, 0>(f, s);
-      case 7: return launch_fdm<T, 112, MODE, 0>(f, s);
-      default: return launch_fdm<T, 128, MODE, 0>(f, s);
+      default: break;
+    }
+    if constexpr (fdm_lds_bytes<T>(128, MODE, 0) <= 160 * 1024) {
+      return f.m <= 112 ? launch_fdm<T, 112, MODE, 0>(f, s) : launch_fdm<T, 128, MODE, 0>(f, s);
+    } else {
+      set_error("middle pair: the tables exceed LDS");
+      return CHEB_ERR_INVALID_ARG;
     }
   }
 }
 
 // split: 0 plain, 1 input through Q^T (the V^{-1} side), 2 output through Q
-// (the V side), 3 the middle pair on a split axis; see k_fdm_wave
+// (the V side); see k_fdm_wave
 template <typename T>
 static int launch_fdm_m(const FdmArgs& f, int mode, int split, hipStream_t s) {
   if (mode == (FDM_MID | FDM_SCALE)) {
-    if (split == 3) return launch_fdm_mode<T, FDM_MID | FDM_SCALE, 3>(f, s);
-    if constexpr (sizeof(T) == sizeof(float)) return launch_fdm_mode<T, FDM_MID | FDM_SCALE, 0>(f, s);
-    set_error("middle pair: FP64 needs a split axis");
-    return CHEB_ERR_INVALID_ARG;
+    if (split) {
+      switch (fdm_width(f.m, true)) {
+        case 32: return launch_fdm_mid<T, 1>(f, s);
+        case 64: return launch_fdm_mid<T, 2>(f, s);
+        case 96: return launch_fdm_mid<T, 3>(f, s);
+        default: return launch_fdm_mid<T, 4>(f, s);
+      }
+    }
+    return launch_fdm_mode<T, FDM_MID | FDM_SCALE, 0>(f, s);
   }
   if (split == 1) {
     switch (mode) {
@@ -1469,21 +1693,53 @@ static int precond_fused(const cheb_plan* p, const T* in, T* out, T* bufA, T* bu
       f.sys = sys;
       f.kc = kc;
     }
-    const int split = p->pc_ax[a].split ? (mode & FDM_MID ? 3 : dir + 1) : 0;
+    const int split = p->pc_ax[a].split ? (dir + 1) : 0;
     return launch_fdm_m<T>(f, mode, split, s);
   };
-  int rc = run(0, 0, in, bufA, FDM_XFULL);
-  // the two z contractions and the scaling between them as one kernel where
-  // both tables fit in LDS (FP64: split axes only)
-  const bool mid = p->pc_ax[2].split || sizeof(T) == sizeof(float);
-  if (!rc) rc = run(1, 0, bufA, bufB, 0);
-  if (mid) {
-    if (!rc) rc = run(2, 0, bufB, bufA, FDM_MID | FDM_SCALE);
-  } else {
-    if (!rc) rc = run(2, 0, bufB, bufA, FDM_SCALE);
-    if (!rc) rc = run(2, 1, bufA, bufB, 0);
-    std::swap(bufA, bufB);
+  // one axis in and out again with the scaling between: one kernel where both
+  // tables fit in LDS, two (through bufB, the result back in bufA) where not
+  auto middle = [&](int a) {
+    if (p->pc_ax[a].split || sizeof(T) == sizeof(float) || m[a] <= 96) {
+      const int rc = run(a, 0, bufA, bufB, FDM_MID | FDM_SCALE);
+      std::swap(bufA, bufB);
+      return rc;
+    }
+    const int rc = run(a, 0, bufA, bufB, FDM_SCALE);
+    return rc ? rc : run(a, 1, bufB, bufA, 0);
+  };
+  // Planes that fit in LDS (the rule of plane_ok; a y axis that is not
+  // mirror-symmetric fits up to 64 nodes): three launches.  An axis at a time takes
+  // five, each streaming the field: 129^3 FP64 82 us against 63, 49^3 29 against
+  // 20, 33^3 24 against 18, 129^3 FP32 64 against 42.
+  const bool sy = p->pc_ax[1].split, sz = p->pc_ax[2].split;
+  if (plane_ok<T>(m[1], m[2], sy, sz)) {
+    PlaneArgs g{};
+    g.gate = offs ? nullptr : p->gate;
+    g.offs = offs;
+    g.m0 = m[0];
+    g.m1 = m[1];
+    g.m2 = m[2];
+    g.nb = nb;
+    auto planes = [&](int dir, const T* X, T* Y) {
+      g.ty = fdm_tab<T>(p, 1, dir, transpose);
+      g.tz = fdm_tab<T>(p, 2, dir, transpose);
+      g.X = X;
+      g.Y = Y;
+      switch (plane_blocks<T>(m[1], m[2], sy, sz)) {
+        case 1: return launch_plane_rb<T, 1>(g, dir == 0, sy, sz, s);
+        case 2: return launch_plane_rb<T, 2>(g, dir == 0, sy, sz, s);
+        case 3: return launch_plane_rb<T, 3>(g, dir == 0, sy, sz, s);
+        default: return launch_plane_rb<T, 4>(g, dir == 0, sy, sz, s);
+      }
+    };
+    int rc = planes(0, in, bufA);
+    if (!rc) rc = middle(0);
+    if (!rc) rc = planes(1, bufA, out);
+    return rc;
   }
+  int rc = run(0, 0, in, bufB, FDM_XFULL);
+  if (!rc) rc = run(1, 0, bufB, bufA, 0);
+  if (!rc) rc = middle(2);
   if (!rc) rc = run(1, 1, bufA, bufB, 0);
   if (!rc) rc = run(0, 1, bufB, out, FDM_YFULL);  // also zeroes the boundary nodes of out
   return rc;

@@ -102,62 +102,97 @@ __global__ __launch_bounds__(kThreads) void k_reduce_cols(const double* __restri
   }
 }
 
-// out = (w - sum_v h_v V_v) * scale; kUE elements per thread per step, with
-// the basis loads of kGroup vectors issued together
+// acc[q] += sum_v c_v V_v at ix[q], v ascending, GR vectors' loads issued together
+// (past the last vector it is read again and not added); ready() runs once behind
+// the first group's loads and makes c readable
+template <typename T, int UE, int GR, typename F>
+__device__ __forceinline__ void add_vectors(const T* __restrict__ V, size_t ld, int nv, const double* c,
+                                            const size_t (&ix)[UE], double (&acc)[UE], F ready) {
+  for (int v = 0; v < nv; v += GR) {
+    T x[GR][UE];
+#pragma unroll
+    for (int g = 0; g < GR; ++g)
+#pragma unroll
+      for (int q = 0; q < UE; ++q) x[g][q] = V[(size_t)(v + g < nv ? v + g : nv - 1) * ld + ix[q]];
+    if (v == 0) ready();
+#pragma unroll
+    for (int g = 0; g < GR; ++g) {
+      if (v + g >= nv) break;
+#pragma unroll
+      for (int q = 0; q < UE; ++q) acc[q] = fma(c[v + g], double(x[g][q]), acc[q]);
+    }
+  }
+}
+
+// Elements per thread and vectors per group of the two kernels below.  Up to
+// kFewPts points a thread has one element and sixteen vectors in flight, which
+// puts the basis of a small grid behind one or two memory latencies; above, there
+// are workgroups enough for four elements.  33^3, 17 vectors: 5.4 us with four elements
+// everywhere, 3.6 us.
+constexpr size_t kFewPts = (size_t)1 << 19;
 constexpr int kUE = 4;
 
-template <typename T>
+// out = (w - sum_v h_v V_v) * scale
+template <typename T, int UE, int GR>
 __global__ __launch_bounds__(kThreads) void k_update_scale(const T* __restrict__ V, size_t ld, int nv,
                                                            const double* __restrict__ h, const T* w, T* out,
                                                            double scale, size_t npts, const double* dscale,
-                                                           const int* gate) {
-  if (gate && !*gate) return;
-  if (dscale) scale = *dscale;
+                                                           const int* gate, const ArnoldiHead* head,
+                                                           ArnoldiHead* host_head) {
   __shared__ double hs[kMaxDots];
-  for (int v = threadIdx.x; v < nv; v += kThreads) hs[v] = h[v];
-  __syncthreads();
-  const size_t step = (size_t)gridDim.x * kThreads * kUE;
-  for (size_t i0 = (size_t)blockIdx.x * kThreads * kUE + threadIdx.x; i0 < npts; i0 += step) {
-    size_t ix[kUE];
-    double acc[kUE];
+  // (the write to the host ends while the vectors are summed, where the kernel
+  // before this one would have to wait for it)
+  if (host_head && blockIdx.x == 0 && threadIdx.x == 0) *host_head = *head;
+  // the flag, the scale and the coefficients are read beside the first vectors
+  const int live = gate ? *gate : 1;
+  if (dscale) scale = *dscale;
+  for (int v = threadIdx.x; v < nv; v += kThreads) hs[v] = -h[v];
+  bool synced = false;
+  const size_t step = (size_t)gridDim.x * kThreads * UE;
+  for (size_t i0 = (size_t)blockIdx.x * kThreads * UE + threadIdx.x; i0 - threadIdx.x < npts; i0 += step) {
+    size_t ix[UE];
+    double acc[UE];
 #pragma unroll
-    for (int q = 0; q < kUE; ++q) {
+    for (int q = 0; q < UE; ++q) {
       const size_t i = i0 + (size_t)q * kThreads;
       ix[q] = i < npts ? i : npts - 1;
       acc[q] = double(w[ix[q]]);
     }
-    int v = 0;
-    for (; v + kGroup <= nv; v += kGroup) {
-      T x[kGroup][kUE];
+    add_vectors<T, UE, GR>(V, ld, nv, hs, ix, acc, [&]() {
+      if (!synced) __syncthreads();
+      synced = true;
+    });
+    if (!live) return;
 #pragma unroll
-      for (int g = 0; g < kGroup; ++g)
-#pragma unroll
-        for (int q = 0; q < kUE; ++q) x[g][q] = V[(size_t)(v + g) * ld + ix[q]];
-#pragma unroll
-      for (int g = 0; g < kGroup; ++g)
-#pragma unroll
-        for (int q = 0; q < kUE; ++q) acc[q] = fma(-hs[v + g], double(x[g][q]), acc[q]);
-    }
-    for (; v < nv; ++v)
-#pragma unroll
-      for (int q = 0; q < kUE; ++q) acc[q] = fma(-hs[v], double(V[(size_t)v * ld + ix[q]]), acc[q]);
-#pragma unroll
-    for (int q = 0; q < kUE; ++q)
+    for (int q = 0; q < UE; ++q)
       if (i0 + (size_t)q * kThreads < npts) out[i0 + (size_t)q * kThreads] = T(acc[q] * scale);
   }
 }
 
-template <typename T>
+template <typename T, int UE, int GR>
 __global__ __launch_bounds__(kThreads) void k_lincomb(const T* __restrict__ V, size_t ld, int nv,
                                                       const double* __restrict__ c, T* out, int accumulate,
                                                       size_t npts) {
   __shared__ double cs[kMaxDots];
   for (int v = threadIdx.x; v < nv; v += kThreads) cs[v] = c[v];
-  __syncthreads();
-  for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < npts; i += (size_t)gridDim.x * kThreads) {
-    double acc = accumulate ? double(out[i]) : 0.0;
-    for (int v = 0; v < nv; ++v) acc = fma(cs[v], double(V[(size_t)v * ld + i]), acc);
-    out[i] = T(acc);
+  bool synced = false;
+  const size_t step = (size_t)gridDim.x * kThreads * UE;
+  for (size_t i0 = (size_t)blockIdx.x * kThreads * UE + threadIdx.x; i0 - threadIdx.x < npts; i0 += step) {
+    size_t ix[UE];
+    double acc[UE];
+#pragma unroll
+    for (int q = 0; q < UE; ++q) {
+      const size_t i = i0 + (size_t)q * kThreads;
+      ix[q] = i < npts ? i : npts - 1;
+      acc[q] = accumulate ? double(out[ix[q]]) : 0.0;
+    }
+    add_vectors<T, UE, GR>(V, ld, nv, cs, ix, acc, [&]() {
+      if (!synced) __syncthreads();
+      synced = true;
+    });
+#pragma unroll
+    for (int q = 0; q < UE; ++q)
+      if (i0 + (size_t)q * kThreads < npts) out[i0 + (size_t)q * kThreads] = T(acc[q]);
   }
 }
 
@@ -333,13 +368,18 @@ int multidot(const T* V, size_t ld, int nv, const T* w, size_t npts, double* par
 
 template <typename T>
 int update_scale(const T* V, size_t ld, int nv, const double* h, const T* w, T* out, double scale,
-                 size_t npts, hipStream_t s, const double* dscale, const int* gate) {
+                 size_t npts, hipStream_t s, const double* dscale, const int* gate, const ArnoldiHead* head,
+                 ArnoldiHead* host_head) {
   if (nv > kMaxDots) {
     set_error("too many vectors in update");
     return CHEB_ERR_INVALID_ARG;
   }
-  hipLaunchKernelGGL(k_update_scale<T>, dim3(grid_for(npts)), dim3(kThreads), 0, s, V, ld, nv, h, w, out,
-                     scale, npts, dscale, gate);
+  if (npts <= kFewPts)
+    hipLaunchKernelGGL((k_update_scale<T, 1, 16>), dim3(grid_for(npts, kThreads)), dim3(kThreads), 0, s, V, ld, nv, h, w,
+                       out, scale, npts, dscale, gate, head, host_head);
+  else
+    hipLaunchKernelGGL((k_update_scale<T, kUE, kGroup>), dim3(grid_for(npts)), dim3(kThreads), 0, s, V, ld, nv, h, w,
+                       out, scale, npts, dscale, gate, head, host_head);
   return hip_check(hipGetLastError(), "update_scale");
 }
 
@@ -350,8 +390,12 @@ int lincomb(const T* V, size_t ld, int nv, const double* c, T* out, int accumula
     set_error("too many vectors in combination");
     return CHEB_ERR_INVALID_ARG;
   }
-  hipLaunchKernelGGL(k_lincomb<T>, dim3(grid_for(npts)), dim3(kThreads), 0, s, V, ld, nv, c, out,
-                     accumulate, npts);
+  if (npts <= kFewPts)
+    hipLaunchKernelGGL((k_lincomb<T, 1, 16>), dim3(grid_for(npts, kThreads)), dim3(kThreads), 0, s, V, ld, nv, c, out,
+                       accumulate, npts);
+  else
+    hipLaunchKernelGGL((k_lincomb<T, kUE, kGroup>), dim3(grid_for(npts)), dim3(kThreads), 0, s, V, ld, nv, c, out,
+                       accumulate, npts);
   return hip_check(hipGetLastError(), "lincomb");
 }
 
@@ -447,7 +491,7 @@ int cc_dot(const double* a, const double* b, const double* wx, const double* wy,
   template int multidot<T>(const T*, size_t, int, const T*, size_t, double*, double*, hipStream_t,    \
                            const int*);                                                               \
   template int update_scale<T>(const T*, size_t, int, const double*, const T*, T*, double, size_t,    \
-                               hipStream_t, const double*, const int*);                               \
+                               hipStream_t, const double*, const int*, const ArnoldiHead*, ArnoldiHead*);                               \
   template int lincomb<T>(const T*, size_t, int, const double*, T*, int, size_t, hipStream_t);        \
   template int axpby<T>(T*, const T*, double, double, size_t, hipStream_t);                           \
   template int copy_scale<T>(T*, const T*, double, size_t, hipStream_t);                              \

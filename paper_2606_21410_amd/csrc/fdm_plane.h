@@ -108,7 +108,7 @@ struct PlaneId {
 
 template <typename T, int RB, bool SY, bool SZ>
 __global__ __launch_bounds__(512) void k_fdm_plane_fwd(PlaneArgs g) {
-  if (g.gate && !*g.gate) return;
+  const int live = g.gate ? *g.gate : 1;  // looked at once the loads are out
   typedef typename Mfma<T>::v4 V4;
   constexpr bool F32 = sizeof(T) == sizeof(float);
   extern __shared__ __align__(16) unsigned char smem[];
@@ -165,6 +165,7 @@ __global__ __launch_bounds__(512) void k_fdm_plane_fwd(PlaneArgs g) {
     }
   }
   __syncthreads();
+  if (!live) return;
   // z: unit = 16 rows and one parity of the modes (half of the row blocks where
   // z is not split); the results replace the rows once every wave has read them
   const int zt = wave >> 1, zp = wave & 1;
@@ -232,7 +233,7 @@ __global__ __launch_bounds__(512) void k_fdm_plane_fwd(PlaneArgs g) {
 
 template <typename T, int RB, bool SY, bool SZ>
 __global__ __launch_bounds__(512) void k_fdm_plane_bwd(PlaneArgs g) {
-  if (g.gate && !*g.gate) return;
+  const int live = g.gate ? *g.gate : 1;  // looked at once the loads are out
   typedef typename Mfma<T>::v4 V4;
   constexpr bool F32 = sizeof(T) == sizeof(float);
   constexpr int HB = SY && RB > 1 ? (RB + 1) / 2 : RB;  // row blocks of a parity per workgroup
@@ -273,6 +274,7 @@ __global__ __launch_bounds__(512) void k_fdm_plane_bwd(PlaneArgs g) {
   plane_copy((const T*)g.ty + b0 * d.sy * 64, ty, part, tid, nt);
   if (SY) plane_copy((const T*)g.ty + (d.by + b0) * d.sy * 64, ty + hb * d.sy * 64, part, tid, nt);
   plane_copy(g.tz, tz, d.ztab() * (int)sizeof(T), tid, nt);
+  if (!live) return;
   {
     // the boundary nodes: this plane's edges, and a share of the field's x faces
     T* P = Y - n2 - 1;

@@ -206,11 +206,10 @@ int arnoldi_begin(ArnoldiState* st, const double* dots, hipStream_t s);
 // re-orthogonalisation, only while pass 0 has paused the cycle for it: it
 // first sets w <- w - V h0 with h0 the pass-0 coefficients); dots[0..j+1]
 // receive the pass's coefficients and ||w||^2; partials:
-// multidot_partials_len(npts, j + 1); host_head (pinned host memory, or null)
-// receives the state's head once the column is done
+// multidot_partials_len(npts, j + 1)
 template <typename T>
 int gram_schmidt(const T* V, size_t ld, int j, T* w, size_t npts, const double* h0, double* partials,
-                 double* dots, ArnoldiState* st, int pass, hipStream_t s, ArnoldiHead* host_head = nullptr);
+                 double* dots, ArnoldiState* st, int pass, hipStream_t s);
 // st->y = R^{-1} g over the cycle's columns
 int arnoldi_solve(ArnoldiState* st, hipStream_t s);
 template <typename T>
@@ -224,10 +223,13 @@ template <typename T>
 int multidot(const T* V, size_t ld, int nv, const T* w, size_t npts, double* partials, double* out,
              hipStream_t s, const int* gate = nullptr);
 // out = (w - sum_i h_i V_i) * scale   (h on device, nv entries; out may alias w);
-// dscale (device) replaces scale when given; gated as multidot
+// dscale (device) replaces scale when given; gated as multidot.  With host_head
+// (pinned host memory), the Arnoldi state's head is copied there, gate or not, so
+// the host reads it once the step's event has completed, with no copy launch.
 template <typename T>
 int update_scale(const T* V, size_t ld, int nv, const double* h, const T* w, T* out, double scale,
-                 size_t npts, hipStream_t s, const double* dscale = nullptr, const int* gate = nullptr);
+                 size_t npts, hipStream_t s, const double* dscale = nullptr, const int* gate = nullptr, const ArnoldiHead* head = nullptr,
+                 ArnoldiHead* host_head = nullptr);
 // out (+)= sum_i c_i V_i  (c on device)
 template <typename T>
 int lincomb(const T* V, size_t ld, int nv, const double* c, T* out, int accumulate, size_t npts,

@@ -64,87 +64,111 @@ __global__ __launch_bounds__(kW) void k_arnoldi_begin(ArnoldiState* st, const do
   st->bprev = beta;
 }
 
-// column j of the Hessenberg matrix from the multi-dot dots[0..j+1], in one
-// wave (lane = 0..63; `col` is LDS scratch of 3 (kMaxKrylovCols + 2) entries)
+// double of lane i (uniform) of a wave
+__device__ __forceinline__ double lane_of(double v, int i) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = __builtin_amdgcn_readlane((int)b, i), hi = __builtin_amdgcn_readlane((int)(b >> 32), i);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// what the Hessenberg column reads of the state, fetched ahead of the column's
+// sums: lane l holds the rotations (and, re-orthogonalising, the column) of rows
+// l and l + 64
+constexpr int kColRegs = (kMaxKrylovCols + kW - 1) / kW;
+struct ColumnIn {
+  ArnoldiHead hd;
+  double cs[kColRegs], sn[kColRegs], h0[kColRegs], g;
+};
+
+__device__ __forceinline__ void column_fetch(const ArnoldiState* st, int j, int pass, int lane, ColumnIn& in) {
+  in.hd = *static_cast<const ArnoldiHead*>(st);
+  in.g = st->g[j];
+#pragma unroll
+  for (int q = 0; q < kColRegs; ++q) {
+    const int i = lane + q * kW, ic = i <= j ? i : j;
+    in.cs[q] = st->cs[ic];
+    in.sn[q] = st->sn[ic];
+    in.h0[q] = pass == 0 ? 0.0 : st->H[ic * kMaxKrylovCols + j];
+  }
+}
+
+// column j of the Hessenberg matrix from the multi-dot dots[0..j+1], in one wave
 // (pass 0: first Gram-Schmidt pass; pass 1: the re-orthogonalisation pass,
 // whose coefficients add to the column), then -- unless pass 0 asks for
 // re-orthogonalisation -- the Givens rotations, the residual estimate
 // |g[j+1]| and the cycle's continuation flag.  The caller has checked that the
 // pass runs (pass 0: the cycle is active; pass 1: re-orthogonalisation asked).
-__device__ void arnoldi_column_wave(ArnoldiState* st, const double* dots, int j, int pass, int lane,
-                                    double* col) {
+// The rotations run over registers, every lane carrying the running entry: a
+// chain of two multiply-adds a row (through LDS, one lane, each row also waited
+// for its reads).
+__device__ __forceinline__ void arnoldi_column_wave(ArnoldiState* st, const double* dots, int j, int pass, int lane,
+                                                    ColumnIn& in) {
   const int ld = kMaxKrylovCols;
-  double* rc_ = col + (kMaxKrylovCols + 2);  // cs[i], sn[i] of the earlier columns, interleaved
-  double ss = 0.0;
-  for (int i = lane; i <= j; i += kW) {
-    const double h = dots[i];
+  ArnoldiHead& hd = in.hd;
+  double ss = 0.0, col[kColRegs];
+#pragma unroll
+  for (int q = 0; q < kColRegs; ++q) {
+    const int i = lane + q * kW;
+    const double h = i <= j ? dots[i] : 0.0;
     ss = fma(h, h, ss);
-    col[i] = pass == 0 ? h : st->H[i * ld + j] + h;
-    if (i < j) {
-      rc_[2 * i] = st->cs[i];
-      rc_[2 * i + 1] = st->sn[i];
-    }
+    col[q] = pass == 0 ? h : in.h0[q] + h;
   }
   ss = wave_sum64(ss);
   const double ww = dots[j + 1];
   const double hh2 = ww - ss;
-  // the lanes' LDS writes of col before lane 0 reads them
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
   if (pass == 0 && !(hh2 > kReorthEta2 * ww)) {
     // cancellation: keep the coefficients and pause the cycle; the host runs
     // the second pass for this column and resumes
-    for (int i = lane; i <= j; i += kW) st->H[i * ld + j] = col[i];
+#pragma unroll
+    for (int q = 0; q < kColRegs; ++q)
+      if (lane + q * kW <= j) st->H[(lane + q * kW) * ld + j] = col[q];
+    hd.reorth = 1;
+    hd.direct = 0;
+    hd.active = 0;
+  } else {
+    const double hn = hh2 > 0.0 ? std::sqrt(hh2) : 0.0;
+    // previous rotations applied to the new column
+    double a = lane_of(col[0], 0);
+#pragma unroll
+    for (int q = 0; q < kColRegs; ++q)
+      for (int l = 0; l < kW && l + q * kW < j; ++l) {
+        const double b = l + 1 < kW ? lane_of(col[q], l + 1) : lane_of(col[q + 1 < kColRegs ? q + 1 : q], 0);
+        const double c = lane_of(in.cs[q], l), s = lane_of(in.sn[q], l);
+        const double t = c * a + s * b;
+        if (lane == l) col[q] = t;
+        a = -s * a + c * b;
+      }
+#pragma unroll
+    for (int q = 0; q < kColRegs; ++q)
+      if (lane + q * kW < j) st->H[(lane + q * kW) * ld + j] = col[q];
+    hd.reorth = 0;
+    hd.hn = hn;
+    hd.inv_hn = hn > 0.0 ? 1.0 / hn : 0.0;
+    const double bb = hn;
+    const double r = std::hypot(a, bb);
+    double c = 1.0, s = 0.0;
+    if (r != 0.0) {
+      c = a / r;
+      s = bb / r;
+    }
+    const double gj = in.g;
+    hd.jend = j + 1;
+    const double est = std::fabs(-s * gj);
+    hd.est = est;
+    hd.breakdown = (!(bb > 1e-300) || !(r > 0.0)) ? 1 : 0;
+    hd.active = (est <= hd.tol || hd.breakdown) ? 0 : 1;
+    // the update that follows forms v_{j+1} unless the cycle ends here
+    hd.direct = hd.active;
     if (lane == 0) {
-      st->reorth = 1;
-      st->direct = 0;
-      st->active = 0;
+      st->cs[j] = c;
+      st->sn[j] = s;
+      st->H[j * ld + j] = r;
+      st->H[(j + 1) * ld + j] = 0.0;
+      st->g[j + 1] = -s * gj;
+      st->g[j] = c * gj;
     }
-    return;
   }
-  const double hn = hh2 > 0.0 ? std::sqrt(hh2) : 0.0;
-  if (lane == 0) {
-    // previous rotations applied to the new column (in LDS)
-    double a = col[0];
-    for (int i = 0; i < j; ++i) {
-      const double b = col[i + 1];
-      const double c = rc_[2 * i], s = rc_[2 * i + 1];
-      col[i] = c * a + s * b;
-      a = -s * a + c * b;
-    }
-    col[j] = a;
-  }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  for (int i = lane; i < j; i += kW) st->H[i * ld + j] = col[i];
-  if (lane != 0) return;
-  st->reorth = 0;
-  st->hn = hn;
-  st->inv_hn = hn > 0.0 ? 1.0 / hn : 0.0;
-  const double a = col[j];
-  const double bb = hn;
-  const double r = std::hypot(a, bb);
-  double c = 1.0, s = 0.0;
-  if (r != 0.0) {
-    c = a / r;
-    s = bb / r;
-  }
-  st->cs[j] = c;
-  st->sn[j] = s;
-  st->H[j * ld + j] = r;
-  st->H[(j + 1) * ld + j] = 0.0;
-  const double gj = st->g[j];
-  st->g[j + 1] = -s * gj;
-  st->g[j] = c * gj;
-  st->jend = j + 1;
-  const double est = std::fabs(-s * gj);
-  st->est = est;
-  st->breakdown = (!(bb > 1e-300) || !(r > 0.0)) ? 1 : 0;
-  st->active = (est <= st->tol || st->breakdown) ? 0 : 1;
-  // the update that follows forms v_{j+1} unless the cycle ends here
-  st->direct = st->active;
+  if (lane == 0) *static_cast<ArnoldiHead*>(st) = hd;
 }
 
 // One Gram-Schmidt pass of Arnoldi step j in two launches: the multi-dot
@@ -155,9 +179,16 @@ __device__ void arnoldi_column_wave(ArnoldiState* st, const double* dots, int j,
 // by w - V h0 with h0 the pass-0 coefficients.  Partial sums are stored
 // column-major ([c][block]) so each column is summed from contiguous memory,
 // always in the same order, so results are reproducible.
+//
+// Pass 0 spreads the groups of four basis vectors over blockIdx.y where the
+// chunks alone do not fill the device (each block then reads w again): a chunk's
+// groups one after the other are a chain of memory latencies.  At 33^3, 18
+// chunks, a pass over 10 to 40 vectors took 7.9 us and takes 4.4 us; from
+// about 4 workgroups per CU on the chunks are enough (129^3, 1049: unchanged).
 constexpr int kGsThreads = 256;
 constexpr int kGsEPT = 8;
 constexpr int kGsChunk = kGsThreads * kGsEPT;
+constexpr int kGsFill = 1024;  // workgroups of a pass-0 launch that the groups are spread up to
 constexpr int kColThreads = 1024;  // the column kernel: one wave per column of partial sums (j < 16 in one round)
 
 template <typename T, int PASS>
@@ -168,7 +199,8 @@ __global__ __launch_bounds__(kGsThreads) void k_gram_schmidt(const T* __restrict
   __shared__ double red[kGsThreads / 64][kMaxKrylovCols + 2];
   __shared__ double hs[kMaxKrylovCols + 2];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  if (PASS == 0 ? !st->active : !st->reorth) return;
+  if (PASS == 1 && !st->reorth) return;
+  const int live = PASS == 0 ? st->active : 1;  // looked at before the store, its load beside the others
   const int nb = gridDim.x;
   const size_t b0 = (size_t)blockIdx.x * kGsChunk;
   double wv[kGsEPT];
@@ -198,7 +230,7 @@ __global__ __launch_bounds__(kGsThreads) void k_gram_schmidt(const T* __restrict
   }
   // basis vectors four at a time, all their loads issued before the products
   // (slots past the last vector load w; every index is clamped into range)
-  for (int v0 = 0; v0 <= nv; v0 += 4) {
+  for (int v0 = 4 * blockIdx.y; v0 <= nv; v0 += 4 * gridDim.y) {
     T x[4][kGsEPT];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
@@ -225,7 +257,9 @@ __global__ __launch_bounds__(kGsThreads) void k_gram_schmidt(const T* __restrict
     }
   }
   __syncthreads();
+  if (!live) return;
   for (int v = tid; v <= nv; v += kGsThreads) {
+    if (v / 4 % gridDim.y != blockIdx.y) continue;
     double sum = 0.0;
 #pragma unroll
     for (int q = 0; q < kGsThreads / 64; ++q) sum += red[q][v];
@@ -235,48 +269,42 @@ __global__ __launch_bounds__(kGsThreads) void k_gram_schmidt(const T* __restrict
 
 // column sums of the nb blocks' partial results (wave q takes columns q,
 // q + 4, ...; lanes stride the blocks), then the Hessenberg column
-// The step's status record (the state's head) then goes to host_head (pinned
-// host memory, or null), written by lane 0 of wave 0 after the column, so the
-// host reads it once the step's event has completed, with no copy launch.
-__device__ __forceinline__ void head_to_host(const ArnoldiState* st, ArnoldiHead* host_head) {
-  static_assert(sizeof(ArnoldiHead) % sizeof(double) == 0, "head copied as doubles");
-  const double* src = reinterpret_cast<const double*>(static_cast<const ArnoldiHead*>(st));
-  double* dst = reinterpret_cast<double*>(host_head);
-#pragma unroll
-  for (int i = 0; i < (int)(sizeof(ArnoldiHead) / sizeof(double)); ++i) dst[i] = src[i];
-}
-
+// (one workgroup, all latency: everything it reads is fetched at once, before the
+// flag is looked at, the first 64 blocks' results of all of a wave's columns
+// together; 33^3: 5.1 us one after the other, 4.6 us so)
 template <int PASS>
 __global__ __launch_bounds__(kColThreads) void k_gs_column(const double* __restrict__ partials, int nb, int nv,
-                                                          double* dots, ArnoldiState* st, int j,
-                                                          ArnoldiHead* host_head) {
+                                                          double* dots, ArnoldiState* st, int j) {
+  constexpr int CW = (kMaxKrylovCols + 1 + kColThreads / 64 - 1) / (kColThreads / 64);  // columns per wave
   __shared__ double hs[kMaxKrylovCols + 2];
-  __shared__ double col[3 * (kMaxKrylovCols + 2)];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  if (PASS == 0 ? !st->active : !st->reorth) {
-    if (host_head && tid == 0) head_to_host(st, host_head);
-    return;
-  }
-  for (int c = wave; c <= nv; c += kColThreads / 64) {
-    const double* pc = partials + (size_t)c * nb;
-    double s4[4] = {0.0, 0.0, 0.0, 0.0};
-    int r = lane;
-    for (; r + 192 < nb; r += 256) {
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  ColumnIn in;
+  column_fetch(st, j, PASS, lane, in);
+  const bool live = PASS == 0 ? in.hd.active : in.hd.reorth;
+  double s4[CW][4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) s4[q] += pc[r + 64 * q];
+  for (int q = 0; q < CW; ++q) {
+    const int c = wave + q * (kColThreads / 64);
+    s4[q][0] = s4[q][1] = s4[q][2] = s4[q][3] = 0.0;
+    if (c <= nv && lane < nb) s4[q][0] = partials[(size_t)c * nb + lane];
+  }
+#pragma unroll
+  for (int q = 0; q < CW; ++q) {
+    const int c = wave + q * (kColThreads / 64);
+    if (c > nv) break;
+    const double* pc = partials + (size_t)c * nb;
+    for (int r = 64 + lane; r < nb; r += 256) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        if (r + 64 * g < nb) s4[q][(g + 1) & 3] += pc[r + 64 * g];
     }
-    for (; r < nb; r += 64) s4[0] += pc[r];
-    double sum = (s4[0] + s4[1]) + (s4[2] + s4[3]);
-    sum = wave_sum64(sum);
+    const double sum = wave_sum64((s4[q][0] + s4[q][1]) + (s4[q][2] + s4[q][3]));
     if (lane == 0) hs[c] = sum;
   }
   __syncthreads();
+  if (!live) return;
   for (int v = tid; v <= nv; v += kColThreads) dots[v] = hs[v];
-  if (wave == 0) {
-    arnoldi_column_wave(st, hs, j, PASS, lane, col);
-    // lane 0 wrote the head's scalars; the other lanes' H writes are not in it
-    if (host_head && lane == 0) head_to_host(st, host_head);
-  }
+  if (wave == 0) arnoldi_column_wave(st, hs, j, PASS, lane, in);
 }
 
 // y = R^{-1} g over the columns the cycle built (back-substitution)
@@ -324,22 +352,22 @@ int arnoldi_begin(ArnoldiState* st, const double* dots, hipStream_t s) {
 
 template <typename T>
 int gram_schmidt(const T* V, size_t ld, int j, T* w, size_t npts, const double* h0, double* partials,
-                 double* dots, ArnoldiState* st, int pass, hipStream_t s, ArnoldiHead* host_head) {
+                 double* dots, ArnoldiState* st, int pass, hipStream_t s) {
   if (j < 0 || j >= kMaxKrylovCols || npts == 0) {
     set_error("Arnoldi column out of range");
     return CHEB_ERR_INVALID_ARG;
   }
   const int nb = (int)((npts + kGsChunk - 1) / kGsChunk);
   if (pass == 0) {
-    hipLaunchKernelGGL((k_gram_schmidt<T, 0>), dim3(nb), dim3(kGsThreads), 0, s, V, ld, j + 1, w, npts, h0,
+    const int groups = (j + 1) / 4 + 1, fill = kGsFill / nb;
+    const int gy = fill < 1 ? 1 : groups < fill ? groups : fill;
+    hipLaunchKernelGGL((k_gram_schmidt<T, 0>), dim3(nb, gy), dim3(kGsThreads), 0, s, V, ld, j + 1, w, npts, h0,
                        partials, st);
-    hipLaunchKernelGGL(k_gs_column<0>, dim3(1), dim3(kColThreads), 0, s, partials, nb, j + 1, dots, st, j,
-                       host_head);
+    hipLaunchKernelGGL(k_gs_column<0>, dim3(1), dim3(kColThreads), 0, s, partials, nb, j + 1, dots, st, j);
   } else {
     hipLaunchKernelGGL((k_gram_schmidt<T, 1>), dim3(nb), dim3(kGsThreads), 0, s, V, ld, j + 1, w, npts, h0,
                        partials, st);
-    hipLaunchKernelGGL(k_gs_column<1>, dim3(1), dim3(kColThreads), 0, s, partials, nb, j + 1, dots, st, j,
-                       host_head);
+    hipLaunchKernelGGL(k_gs_column<1>, dim3(1), dim3(kColThreads), 0, s, partials, nb, j + 1, dots, st, j);
   }
   return hip_check(hipGetLastError(), "gram_schmidt");
 }
@@ -356,9 +384,9 @@ int scale_by(T* v, const double* dscale, size_t npts, hipStream_t s) {
 }
 
 template int gram_schmidt<double>(const double*, size_t, int, double*, size_t, const double*, double*, double*,
-                                  ArnoldiState*, int, hipStream_t, ArnoldiHead*);
+                                  ArnoldiState*, int, hipStream_t);
 template int gram_schmidt<float>(const float*, size_t, int, float*, size_t, const double*, double*, double*,
-                                 ArnoldiState*, int, hipStream_t, ArnoldiHead*);
+                                 ArnoldiState*, int, hipStream_t);
 template int scale_by<double>(double*, const double*, size_t, hipStream_t);
 template int scale_by<float>(float*, const double*, size_t, hipStream_t);
 

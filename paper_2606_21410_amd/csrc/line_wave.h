@@ -50,7 +50,7 @@ __host__ __device__ constexpr int wave_simd_waves(int MT, int MODE, int NW) {
 
 template <typename T, int MT, int MODE, bool FIRST, bool CG, int NW>
 __global__ __launch_bounds__(64 * NW, wave_simd_waves<T>(MT, MODE, NW)) void k_line_wave(LineArgs<T> a) {
-  if (a.gate && !*a.gate) return;
+  const int live = a.gate ? *a.gate : 1;  // looked at once the first loads are out
   typedef typename Mfma<T>::v4 V4;
   constexpr bool FULL = MODE == LINE_FULL, DMUL = MODE == LINE_DMUL, DER = MODE == LINE_DERIV || DMUL;
   constexpr bool JAC = MODE == LINE_JAC;
@@ -206,6 +206,7 @@ __global__ __launch_bounds__(64 * NW, wave_simd_waves<T>(MT, MODE, NW)) void k_l
       if (tid + i * NT < W) dst[tid + i * NT] = v[i];
   }
   lds_barrier();
+  if (!live) return;
 
   // z pencils in a face: every node is a boundary node of the reduced system
   bool clear = FIRST && !ALLP;

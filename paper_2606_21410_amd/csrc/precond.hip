@@ -862,7 +862,7 @@ __host__ __device__ constexpr int fdm_mid_lds() {
 
 template <typename T, int RB>
 __global__ __launch_bounds__(64 * kMidWaves) void k_fdm_mid(FdmArgs g) {
-  if (g.gate && !*g.gate) return;
+  const int live = g.gate ? *g.gate : 1;  // looked at once the loads are out
   constexpr int KS = 4 * RB, TAB = fdm_tab_elems(32 * RB, 1), NT = 64 * kMidWaves;
   constexpr int HO = (RB + 1) / 2;  // row blocks whose nodes the symmetric wave stores
   constexpr bool F32 = sizeof(T) == sizeof(float);
@@ -944,6 +944,7 @@ __global__ __launch_bounds__(64 * kMidWaves) void k_fdm_mid(FdmArgs g) {
     load();
   }
   barrier();
+  if (!live) return;
   const int a0 = axis == 0 ? 1 : 0, a1 = axis == 2 ? 1 : 2;
   const T* tA = tabA + par * RB * KS * 64 + lane;
   const T* tB = tabB + par * RB * KS * 64 + lane;

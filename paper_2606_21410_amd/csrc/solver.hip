@@ -241,11 +241,11 @@ int lgmres(cheb_plan* p, ApplyFn&& A, const T* b, T* x, bool x_zero, double tol_
       T* wj = (j & 1) ? kw.w2 : w;
       int r = A(dir, wj);
       p->gate = nullptr;
-      // the column kernel also writes the step's head to its pinned ring slot
-      if (!r) r = gram_schmidt<T>(kw.V, ld, j, wj, npts, nullptr, sc.partials, sc.dots, ast, 0, s, &ring[j & 1]);
+      // the update also writes the step's head to its pinned ring slot
+      if (!r) r = gram_schmidt<T>(kw.V, ld, j, wj, npts, nullptr, sc.partials, sc.dots, ast, 0, s);
       if (!r)
         r = update_scale<T>(kw.V, ld, j + 1, sc.dots, wj, kw.V + (size_t)(j + 1) * ld, 1.0, npts, s, &ast->inv_hn,
-                            &ast->direct);
+                            &ast->direct, ast, &ring[j & 1]);
       return r;
     };
     auto fetch_now = [&](ArnoldiHead* out) -> int {

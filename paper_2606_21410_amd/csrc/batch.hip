@@ -43,8 +43,13 @@ struct ApplyGroup {
   std::vector<int> hact;      // host copy of the active list last uploaded
 };
 
+// Systems whose preconditioner runs as one launch sequence: the same box and face
+// types, or (merged) the same box and any face types that precond_mergeable takes,
+// each with its own tables: the load cases of one box are three sets of face types,
+// and a launch for each left the device to a few planes.
 struct PrecGroup {
   int rep;
+  bool merged = false;
   std::vector<int> members;
   size_t pack_off = 0;         // its region of the packed preconditioner scratch
   long long* doffs = nullptr;  // device: packed offsets of the active members
@@ -68,6 +73,9 @@ struct cheb_batch {
   size_t P;  // packed length in elements
   std::vector<cheb::ApplyGroup> groups;
   std::vector<cheb::PrecGroup> pgroups;
+  std::vector<int> prep;        // system whose plan holds a system's preconditioner factors
+  cheb::PcTables* dpct;         // device: their tables by system, [FP64, FP32] (null: none merged)
+  int pct_ready;
   // segmented-kernel chunk table (device)
   int nchunks;
   int* ch_sys;
@@ -567,7 +575,8 @@ int bprec(cheb_batch* B, const T* in, T* out, T* pa, T* pb) {
     hipStream_t st = fork ? B->side[i % kSide] : B->stream;
     ++i;
     rc = precond_apply_batch<T>(B->plans[g.rep], in, out, g.doffs, g.dsys, B->dkc, (int)g.hact.size(), B->P,
-                                pa + g.pack_off, pb + g.pack_off, st);
+                                pa + g.pack_off, pb + g.pack_off, st,
+                                g.merged ? B->dpct + (sizeof(T) == sizeof(double) ? 0 : B->nprob) : nullptr);
     if (rc) break;
   }
   if (fork) {
@@ -897,6 +906,8 @@ int cheb_batch_create(const cheb_grid* grids, int32_t nprob, int32_t precision, 
   B->ws = nullptr;
   B->ws_bytes = 0;
   B->side_ok = 0;
+  B->dpct = nullptr;
+  B->pct_ready = 0;
   int rc = CHEB_OK;
   auto fail = [&](int code) {
     cheb_batch_destroy(B);
@@ -920,6 +931,7 @@ int cheb_batch_create(const cheb_grid* grids, int32_t nprob, int32_t precision, 
         return false;
     return true;
   };
+  bool any_merged = false;
   for (int s = 0; s < nprob; ++s) {
     bool placed = false;
     for (auto& g : B->groups)
@@ -936,9 +948,14 @@ int cheb_batch_create(const cheb_grid* grids, int32_t nprob, int32_t precision, 
       g.dense = p->dd_ok[0] && p->dd_ok[1] && p->dd_ok[2];
       B->groups.push_back(g);
     }
+    int src = s;  // the first system of the same box and face types
+    for (int q = 0; q < s && src == s; ++q)
+      if (same_box(q, s) && std::memcmp(grids[q].bc, grids[s].bc, sizeof(grids[s].bc)) == 0) src = q;
+    B->prep.push_back(src);
     bool pplaced = false;
     for (auto& g : B->pgroups)
-      if (same_box(g.rep, s) && std::memcmp(grids[g.rep].bc, grids[s].bc, sizeof(grids[s].bc)) == 0) {
+      if (same_box(g.rep, s) && ((g.merged && precond_mergeable(grids[s])) ||
+                                 std::memcmp(grids[g.rep].bc, grids[s].bc, sizeof(grids[s].bc)) == 0)) {
         g.members.push_back(s);
         pplaced = true;
         break;
@@ -946,6 +963,8 @@ int cheb_batch_create(const cheb_grid* grids, int32_t nprob, int32_t precision, 
     if (!pplaced) {
       PrecGroup g;
       g.rep = s;
+      g.merged = precond_mergeable(grids[s]);
+      any_merged = any_merged || g.merged;
       g.members.push_back(s);
       B->pgroups.push_back(g);
     }
@@ -964,6 +983,8 @@ int cheb_batch_create(const cheb_grid* grids, int32_t nprob, int32_t precision, 
     if (!rc) rc = hip_check(hipMalloc((void**)&g.dact, nm * sizeof(int)), "hipMalloc(batch table)");
     if (!rc) rc = hip_check(hipMemcpy(g.dsys, tab.data(), nm * sizeof(DenseSys), hipMemcpyHostToDevice), "hipMemcpy");
   }
+  if (any_merged && !rc)
+    rc = hip_check(hipMalloc((void**)&B->dpct, 2 * (size_t)nprob * sizeof(PcTables)), "hipMalloc(batch table)");
   size_t pack = 0;
   for (auto& g : B->pgroups) {
     const size_t nm = g.members.size();
@@ -1163,9 +1184,17 @@ int cheb_batch_solve(cheb_batch* batch, const void* const* K, const void* const*
   if (rc) return rc;
   if (bp.precond) {
     std::vector<double> kc(ns);
-    // a group's batched contractions read only its representative's factors
-    for (const auto& g : B->pgroups)
-      if (!rc) rc = precond_setup(B->plans[g.rep]);
+    // the batched contractions read the factors of the first system of a box and
+    // set of face types
+    for (int s = 0; s < ns; ++s)
+      if (!rc) rc = precond_setup(B->plans[B->prep[s]]);
+    if (!rc && B->dpct && !B->pct_ready) {
+      std::vector<PcTables> t(2 * (size_t)ns);
+      for (int s = 0; s < ns; ++s)
+        for (int f = 0; f < 2; ++f) t[(size_t)f * ns + s] = precond_tables(B->plans[B->prep[s]], f != 0);
+      rc = hip_check(hipMemcpy(B->dpct, t.data(), t.size() * sizeof(PcTables), hipMemcpyHostToDevice), "hipMemcpy(tables)");
+      if (!rc) B->pct_ready = 1;
+    }
     for (int s = 0; s < ns && !rc; ++s)
       rc = vsum<double>((const double*)K[s], B->npts[s], w.sc.partials, w.sc.dots + s, st);
     double* hp = B->hpin;
@@ -1330,6 +1359,7 @@ int cheb_batch_destroy(cheb_batch* batch) {
     if (g.dsys) (void)hipFree(g.dsys);
     if (g.dact) (void)hipFree(g.dact);
   }
+  (void)hipFree(batch->dpct);
   for (auto& g : batch->pgroups) {
     if (g.doffs) (void)hipFree(g.doffs);
     if (g.dsys) (void)hipFree(g.dsys);

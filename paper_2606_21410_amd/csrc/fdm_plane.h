@@ -44,6 +44,8 @@ struct PlaneArgs {
   const void* X;          // forward: full fields, backward: packed modes
   void* Y;                // forward: packed modes, backward: full fields
   const long long* offs;  // field b starts at offs[b] (null: b * n0 n1 n2)
+  const PcTables* mem;    // batches of mixed face types: tables of system sys[b] (null: ty, tz)
+  const int* sys;
   int m0, m1, m2, nb;
   int halves;             // workgroups per plane (set by the launch)
 };
@@ -126,6 +128,8 @@ __global__ __launch_bounds__(512) void k_fdm_plane_fwd(PlaneArgs g) {
   T* ty = (T*)smem;
   T* tz = ty + d.ytab(true);
   T* S = tz + d.ztab();
+  const T* gy = (const T*)(g.mem ? g.mem[g.sys[b]].in[1] : g.ty);
+  const T* gz = (const T*)(g.mem ? g.mem[g.sys[b]].in[2] : g.tz);
   const int ld = d.ld, rows = d.rows(true);
   const int h = id.h, rin = SY ? (h ? m1 - ps1 : ps1) : m1;  // rows of this half
   // the plane's rows (or their pair sums or differences; the middle row twice, its
@@ -146,8 +150,8 @@ __global__ __launch_bounds__(512) void k_fdm_plane_fwd(PlaneArgs g) {
     }
   };
   load(wave);
-  plane_copy((const T*)g.ty + h * d.ytab(true), ty, d.ytab(true) * (int)sizeof(T), tid, nt);
-  plane_copy(g.tz, tz, d.ztab() * (int)sizeof(T), tid, nt);
+  plane_copy(gy + h * d.ytab(true), ty, d.ytab(true) * (int)sizeof(T), tid, nt);
+  plane_copy(gz, tz, d.ztab() * (int)sizeof(T), tid, nt);
   for (int r0 = wave; r0 < rows; r0 += QR * nw) {
     if (r0 != wave) load(r0);
 #pragma unroll
@@ -248,6 +252,8 @@ __global__ __launch_bounds__(512) void k_fdm_plane_bwd(PlaneArgs g) {
   const int b = id.plane / g.m0, i0 = id.plane - b * g.m0;
   const T* X = (const T*)g.X + (long long)id.plane * m1 * m2;
   T* Y = (T*)g.Y + (g.offs ? g.offs[b] : (long long)b * n0 * n1 * n2) + ((long long)(i0 + 1) * n1 + 1) * n2 + 1;
+  const T* gy = (const T*)(g.mem ? g.mem[g.sys[b]].out[1] : g.ty);
+  const T* gz = (const T*)(g.mem ? g.mem[g.sys[b]].out[2] : g.tz);
   const int ld = d.ld, rows = d.rows(false), hb = d.hb, b0 = id.h * hb;
   const int nyb = b0 + hb <= d.by ? hb : d.by - b0;  // row blocks of a parity of this half
   T* ty = (T*)smem;
@@ -271,9 +277,9 @@ __global__ __launch_bounds__(512) void k_fdm_plane_bwd(PlaneArgs g) {
     }
   }
   const int part = nyb * d.sy * 64 * (int)sizeof(T);
-  plane_copy((const T*)g.ty + b0 * d.sy * 64, ty, part, tid, nt);
-  if (SY) plane_copy((const T*)g.ty + (d.by + b0) * d.sy * 64, ty + hb * d.sy * 64, part, tid, nt);
-  plane_copy(g.tz, tz, d.ztab() * (int)sizeof(T), tid, nt);
+  plane_copy(gy + b0 * d.sy * 64, ty, part, tid, nt);
+  if (SY) plane_copy(gy + (d.by + b0) * d.sy * 64, ty + hb * d.sy * 64, part, tid, nt);
+  plane_copy(gz, tz, d.ztab() * (int)sizeof(T), tid, nt);
   if (!live) return;
   {
     // the boundary nodes: this plane's edges, and a share of the field's x faces

@@ -57,6 +57,14 @@ struct PrecondAxis {
   size_t off_tab[2][2];  // an axis with the same 1-D problem as an earlier one shares its tables
 };
 
+// device addresses of one system's preconditioner tables in one precision: the
+// fragment tables of the way in and out per axis, the eigenvalues
+struct PcTables {
+  const void* in[3];
+  const void* out[3];
+  const void* lam[3];
+};
+
 }  // namespace cheb
 
 struct cheb_plan {
@@ -279,7 +287,12 @@ int precond_apply(const cheb_plan* p, const T* in, T* out, T* bufA, T* bufB, dou
 // span = elements of the packed batch (every offs[k] + field size is within it)
 template <typename T>
 int precond_apply_batch(const cheb_plan* rep, const T* in, T* out, const long long* offs, const int* sys,
-                        const double* kc, int nmem, size_t span, T* bufA, T* bufB, hipStream_t s);
+                        const double* kc, int nmem, size_t span, T* bufA, T* bufB, hipStream_t s,
+                        const PcTables* mem = nullptr);
+// whether systems of this box and size may share a batched application whatever
+// their face types (mem: tables by system id, of plans whose precond_setup has run)
+bool precond_mergeable(const cheb_grid& g);
+PcTables precond_tables(const cheb_plan* p, bool f32);
 // sum of all entries (double accumulation) into out[0]
 template <typename T>
 int vsum(const T* x, size_t npts, double* partials, double* out, hipStream_t s);

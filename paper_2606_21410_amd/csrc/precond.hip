@@ -684,6 +684,7 @@ struct FdmArgs {
   double inv_k;               // 1 / Kc of a single system (sys == null)
   const int* sys;             // batch: Kc of block b is kc[sys[b]]
   const double* kc;
+  const PcTables* mem;        // k_fdm_mid: tables of system sys[b] (null: tab, tab2, lam0..2)
 };
 
 // fusion modes: X is a full field / Y is a full field / Y is scaled / the
@@ -880,21 +881,24 @@ __global__ __launch_bounds__(64 * kMidWaves) void k_fdm_mid(FdmArgs g) {
   T* Y = (T*)g.Y;
   const int plane = g.m1 * g.m2, bsz = plane * g.m0;
   const int st0 = axis == 2 ? 1 : axis == 1 ? g.m2 : plane;
-  const int ppb = bsz / m, npen = ppb * g.nb, ntasks = (npen + 15) / 16;
+  const int npen = bsz / m, ntasks = (npen + 15) / 16;  // of a block
+  const int bi = blockIdx.y;
+  PcTables tabs{{g.tab, g.tab, g.tab}, {g.tab2, g.tab2, g.tab2}, {g.lam0, g.lam1, g.lam2}};
+  if (g.mem) tabs = g.mem[g.sys[bi]];
+  X += (long long)bi * bsz;
+  Y += (long long)bi * bsz;
   bool valid = false;
   long long bx = 0;
-  int ia = 0, ib = 0, bi = 0;
+  int ia = 0, ib = 0;
   auto locate = [&](int task) __attribute__((always_inline)) {
     const int q = task * 16 + li;
     valid = q < npen;
     if (!valid) return;
-    bi = q / ppb;
-    const int qq = q - bi * ppb;
     // the pencil's indices across the axis
     const int w = axis == 2 ? g.m1 : g.m2;
-    ia = qq / w;
-    ib = qq - ia * w;
-    bx = (long long)bi * bsz + (axis == 0 ? (long long)qq : axis == 1 ? (long long)ia * plane + ib : (long long)qq * g.m2);
+    ia = q / w;
+    ib = q - ia * w;
+    bx = axis == 0 ? q : axis == 1 ? (long long)ia * plane + ib : (long long)q * g.m2;
   };
   T xl[KS], xh[KS];
   // (the stride is renewed for every use, or the offsets of all the rows stay in
@@ -925,9 +929,9 @@ __global__ __launch_bounds__(64 * kMidWaves) void k_fdm_mid(FdmArgs g) {
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
   };
-  fetch(g.tab);
+  fetch(axis == 0 ? tabs.in[0] : axis == 1 ? tabs.in[1] : tabs.in[2]);
   {
-    const T* lp[3] = {(const T*)g.lam0, (const T*)g.lam1, (const T*)g.lam2};
+    const T* lp[3] = {(const T*)tabs.lam[0], (const T*)tabs.lam[1], (const T*)tabs.lam[2]};
     const int md[3] = {g.m0, g.m1, g.m2};
     if (tid < 3 * 128) {
       const int a = tid >> 7, i = tid & 127;
@@ -935,7 +939,7 @@ __global__ __launch_bounds__(64 * kMidWaves) void k_fdm_mid(FdmArgs g) {
     }
   }
   put(tabA);
-  fetch(g.tab2);
+  fetch(axis == 0 ? tabs.out[0] : axis == 1 ? tabs.out[1] : tabs.out[2]);
   put(tabB);
   int base = blockIdx.x * (kMidWaves / 2);
   const int task0 = base + (wave >> 1);
@@ -1509,7 +1513,11 @@ static int launch_fdm_mid(const FdmArgs& f, hipStream_t s) {
   static DeviceCache cache;
   int resident = 0;
   if (int rc = fdm_resident((const void*)k_fdm_mid<T, RB>, 64 * kMidWaves, lds, cache, &resident)) return rc;
-  hipLaunchKernelGGL((k_fdm_mid<T, RB>), dim3(fdm_grid(f, kMidWaves / 2, resident)), dim3(64 * kMidWaves), lds, s, f);
+  // a row of workgroups per block, persistent within it
+  const long long tasks = ((long long)f.m0 * f.m1 * f.m2 / f.m + 15) / 16;
+  const int need = (int)((tasks + kMidWaves / 2 - 1) / (kMidWaves / 2));
+  const int most = resident / f.nb > 0 ? resident / f.nb : 1;
+  hipLaunchKernelGGL((k_fdm_mid<T, RB>), dim3(need < most ? need : most, f.nb), dim3(64 * kMidWaves), lds, s, f);
   return hip_check(hipGetLastError(), "middle pair");
 }
 
@@ -1668,7 +1676,8 @@ static bool fused_ok(const int* m, int nb) {
 // contraction also zeroes the boundary nodes of the output.
 template <typename T>
 static int precond_fused(const cheb_plan* p, const T* in, T* out, T* bufA, T* bufB, bool transpose, int nb,
-                         const long long* offs, double inv_k, const int* sys, const double* kc, hipStream_t s) {
+                         const long long* offs, double inv_k, const int* sys, const double* kc, const PcTables* mem,
+                         hipStream_t s) {
   const int n0 = p->g.n[0], n1 = p->g.n[1], n2 = p->g.n[2];
   const int m[3] = {n0 - 2, n1 - 2, n2 - 2};
   const T* base = pc_base<T>(p);
@@ -1693,6 +1702,7 @@ static int precond_fused(const cheb_plan* p, const T* in, T* out, T* bufA, T* bu
       f.inv_k = inv_k;
       f.sys = sys;
       f.kc = kc;
+      f.mem = mem;
     }
     const int split = p->pc_ax[a].split ? (dir + 1) : 0;
     return launch_fdm_m<T>(f, mode, split, s);
@@ -1717,6 +1727,8 @@ static int precond_fused(const cheb_plan* p, const T* in, T* out, T* bufA, T* bu
     PlaneArgs g{};
     g.gate = offs ? nullptr : p->gate;
     g.offs = offs;
+    g.mem = mem;
+    g.sys = sys;
     g.m0 = m[0];
     g.m1 = m[1];
     g.m2 = m[2];
@@ -1746,13 +1758,32 @@ static int precond_fused(const cheb_plan* p, const T* in, T* out, T* bufA, T* bu
   return rc;
 }
 
+bool precond_mergeable(const cheb_grid& g) {
+  const int m1 = g.n[1] - 2, m2 = g.n[2] - 2;
+  for (int a = 0; a < 3; ++a)
+    if (g.n[a] - 2 > 128 || g.bc[2 * a] != g.bc[2 * a + 1] || g.robin[2 * a] != g.robin[2 * a + 1]) return false;
+  return plane_ok<double>(m1, m2, true, true) && plane_ok<float>(m1, m2, true, true);
+}
+
+template <typename T>
+static PcTables tables_of(const cheb_plan* p) {
+  PcTables t;
+  for (int a = 0; a < 3; ++a) {
+    t.in[a] = fdm_tab<T>(p, a, 0, false);
+    t.out[a] = fdm_tab<T>(p, a, 1, false);
+    t.lam[a] = pc_base<T>(p) + p->pc_ax[a].off_lam;
+  }
+  return t;
+}
+PcTables precond_tables(const cheb_plan* p, bool f32) { return f32 ? tables_of<float>(p) : tables_of<double>(p); }
+
 template <typename T>
 int precond_apply(const cheb_plan* p, const T* in, T* out, T* bufA, T* bufB, double kc, bool transpose,
                   hipStream_t s) {
   const int n0 = p->g.n[0], n1 = p->g.n[1], n2 = p->g.n[2];
   const int m[3] = {n0 - 2, n1 - 2, n2 - 2};
   if (fused_ok(m, 1))
-    return precond_fused<T>(p, in, out, bufA, bufB, transpose, 1, nullptr, 1.0 / kc, nullptr, nullptr, s);
+    return precond_fused<T>(p, in, out, bufA, bufB, transpose, 1, nullptr, 1.0 / kc, nullptr, nullptr, nullptr, s);
   const size_t tot = (size_t)m[0] * m[1] * m[2];
   const T* base = pc_base<T>(p);
   hipLaunchKernelGGL(k_pack_interior<T>, dim3(grid1(tot)), dim3(256), 0, s, in, bufA, n0, n1, n2);
@@ -1794,13 +1825,13 @@ int mfma_gemm(const T* A, const T* B, T* D, int I, int K, int C, hipStream_t s) 
 
 template <typename T>
 int precond_apply_batch(const cheb_plan* rep, const T* in, T* out, const long long* offs, const int* sys,
-                        const double* kc, int nmem, size_t span, T* bufA, T* bufB, hipStream_t s) {
+                        const double* kc, int nmem, size_t span, T* bufA, T* bufB, hipStream_t s, const PcTables* mem) {
   if (nmem <= 0) return CHEB_OK;
   const int n0 = rep->g.n[0], n1 = rep->g.n[1], n2 = rep->g.n[2];
   const int m[3] = {n0 - 2, n1 - 2, n2 - 2};
   (void)span;
   if (fused_ok(m, nmem))
-    return precond_fused<T>(rep, in, out, bufA, bufB, false, nmem, offs, 0.0, sys, kc, s);
+    return precond_fused<T>(rep, in, out, bufA, bufB, false, nmem, offs, 0.0, sys, kc, mem, s);
   const size_t tot = (size_t)m[0] * m[1] * m[2];
   const T* base = pc_base<T>(rep);
   hipLaunchKernelGGL(k_pack_interior_b<T>, dim3(grid1(tot), nmem), dim3(256), 0, s, in, offs, bufA, n0, n1, n2);
@@ -1826,9 +1857,9 @@ int precond_apply_batch(const cheb_plan* rep, const T* in, T* out, const long lo
 }
 
 template int precond_apply_batch<double>(const cheb_plan*, const double*, double*, const long long*, const int*,
-                                         const double*, int, size_t, double*, double*, hipStream_t);
+                                         const double*, int, size_t, double*, double*, hipStream_t, const PcTables*);
 template int precond_apply_batch<float>(const cheb_plan*, const float*, float*, const long long*, const int*,
-                                        const double*, int, size_t, float*, float*, hipStream_t);
+                                        const double*, int, size_t, float*, float*, hipStream_t, const PcTables*);
 template int precond_apply<double>(const cheb_plan*, const double*, double*, double*, double*, double, bool,
                                    hipStream_t);
 template int precond_apply<float>(const cheb_plan*, const float*, float*, float*, float*, double, bool,

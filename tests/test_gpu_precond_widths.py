@@ -60,3 +60,32 @@ def test_precond_widths(shape, bc, prec):
         assert np.linalg.norm(got[1:-1, 1:-1, 1:-1] - x) <= tol * np.linalg.norm(x)
         got[1:-1, 1:-1, 1:-1] = 0
         assert not got.any()
+
+
+@pytest.mark.parametrize("precision", ["f64", "mixed"])
+def test_batch_precond_of_mixed_face_types(precision):
+    """Systems of one box whose face types differ share a batched application with
+    tables of their own; one that is not mirror-symmetric, another box and a
+    system that stops early run beside them."""
+    require_gpu()
+    import torch
+    from paper_2606_21410_amd import workloads as W
+    from paper_2606_21410_amd.api import Batch, SolveOptions
+    from tests.gpu_util import rel_l2
+    n, m = (20, 35, 18), (9, 12, 10)
+    lo, hi = (0.0, 0.0, 0.0), (1.0, 1.0, 1.0)
+    bcs = [(0, 0, 1, 1, 1, 1), (1, 1, 0, 0, 1, 1), (1, 1, 1, 1, 0, 0), (0, 0, 1, 1, 1, 1), (0, 1, 0, 0, 1, 1)]
+    grids = [(n, lo, hi, b) for b in bcs] + [(m, lo, hi, bcs[1])]
+    d = lambda a: to_dev(a, torch.float64)
+    Ks, fs, gs, refs = [], [], [], []
+    for i, (sh, _, _, bc) in enumerate(grids):
+        K = np.full(sh, 1.5) if i == 1 else W.random_conductivity(sh, 20 + i, 0.3)
+        f = W.random_field(sh, 30 + i)
+        g = W.random_faces(W.Grid(sh, lo, hi, bc), 40 + i)
+        Ks.append(d(K)), fs.append(d(f)), gs.append(d(g))
+        refs.append(O.solve(O.Grid3(sh, lo, hi, bc), K, f, g, tol=1e-14))
+    us, infos = Batch(grids, precision).solve(Ks, fs, gs, opts=SolveOptions(rtol=1e-11, maxiter=4000, precond=True))
+    for i, (u, info, ref) in enumerate(zip(us, infos, refs)):
+        log(f"batch {precision} system {i}: {info}")
+        assert info["status"] == 0
+        assert rel_l2(to_host(u), ref) <= 1e-8

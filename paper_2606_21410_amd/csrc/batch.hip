@@ -50,6 +50,7 @@ struct ApplyGroup {
 struct PrecGroup {
   int rep;
   bool merged = false;
+  int box = 0;                 // representative of the apply group of the same box
   std::vector<int> members;
   size_t pack_off = 0;         // its region of the packed preconditioner scratch
   long long* doffs = nullptr;  // device: packed offsets of the active members
@@ -88,7 +89,7 @@ struct cheb_batch {
   std::vector<int> hchl;
   std::vector<int> sys_c0_h, sys_nc_h;
   double* dcoef;  // nprob x kMaxCoef per-system coefficients
-  double* dscal;  // nprob x 8 per-system scalars
+  double* dscal;  // nprob x 8 per-system scalars, behind dcoef in one allocation
   double* dkc;    // nprob mean conductivities
   int* dflag;
   double* hpin;   // pinned host staging: nprob x (kMaxCoef + 8) x 2 doubles
@@ -401,6 +402,16 @@ int upload(cheb_batch* B, double* dev, const double* host_src, size_t count, int
                    "hipMemcpyAsync(H2D)");
 }
 
+// both tables of a step as one copy
+int upload_both(cheb_batch* B, const std::vector<double>& coef, const std::vector<double>& scal) {
+  double* hp = B->hpin;
+  std::memcpy(hp, coef.data(), coef.size() * sizeof(double));
+  std::memcpy(hp + coef.size(), scal.data(), scal.size() * sizeof(double));
+  return hip_check(hipMemcpyAsync(B->dcoef, hp, (coef.size() + scal.size()) * sizeof(double), hipMemcpyHostToDevice,
+                                  B->stream),
+                   "hipMemcpyAsync(H2D)");
+}
+
 template <typename T>
 int bdots(cheb_batch* B, const T* V, size_t ld, int nv, const T* w, BScratch& sc, std::vector<double>& out) {
   const int nv1 = nv + 1;
@@ -522,10 +533,22 @@ int side_join(cheb_batch* B, int used) {
   return rc;
 }
 
-// y = A x for the active systems (reduced operator, packed fields); the
-// groups are independent and run on the side streams
+// the preconditioner of one group's active members on stream st; each group packs
+// its members' interiors into its own region of pa / pb
 template <typename T>
-int bapply(cheb_batch* B, const T* K, const T* x, T* y) {
+int bprec_group(cheb_batch* B, const PrecGroup& g, const T* in, T* out, T* pa, T* pb, hipStream_t st) {
+  return precond_apply_batch<T>(B->plans[g.rep], in, out, g.doffs, g.dsys, B->dkc, (int)g.hact.size(), B->P,
+                                pa + g.pack_off, pb + g.pack_off, st,
+                                g.merged ? B->dpct + (sizeof(T) == sizeof(double) ? 0 : B->nprob) : nullptr);
+}
+
+// y = A x for the active systems (reduced operator, packed fields); the
+// groups are independent and run on the side streams.  With `in`, x is first set
+// to M^{-1} in, each group's preconditioner in front of its operator on the same
+// stream (a fork and a join between them cost two rounds of events a step)
+template <typename T>
+int bapply(cheb_batch* B, const T* K, const T* x, T* y, const T* in = nullptr, T* px = nullptr, T* pa = nullptr,
+           T* pb = nullptr) {
   int nact = 0;
   for (auto& g : B->groups) nact += g.hact.empty() ? 0 : 1;
   const bool fork = B->side_ok && nact > 1;
@@ -537,6 +560,11 @@ int bapply(cheb_batch* B, const T* K, const T* x, T* y) {
     if (g.hact.empty()) continue;
     hipStream_t st = fork ? B->side[i % kSide] : B->stream;
     ++i;
+    if (in)
+      for (auto& pg : B->pgroups) {
+        if (rc || pg.hact.empty() || pg.box != g.rep) continue;
+        rc = bprec_group<T>(B, pg, in, px, pa, pb, st);
+      }
     const cheb_plan* rep = B->plans[g.rep];
     if (g.dense) {
       for (int pass = 0; pass < 3 && !rc; ++pass) {
@@ -560,8 +588,8 @@ int bapply(cheb_batch* B, const T* K, const T* x, T* y) {
   return rc;
 }
 
-// each group packs its members' interiors into its own region of pa / pb, so
-// the groups can run concurrently on the side streams
+// the groups write regions of their own, so they can run concurrently on the side
+// streams
 template <typename T>
 int bprec(cheb_batch* B, const T* in, T* out, T* pa, T* pb) {
   int nact = 0;
@@ -574,9 +602,7 @@ int bprec(cheb_batch* B, const T* in, T* out, T* pa, T* pb) {
     if (g.hact.empty()) continue;
     hipStream_t st = fork ? B->side[i % kSide] : B->stream;
     ++i;
-    rc = precond_apply_batch<T>(B->plans[g.rep], in, out, g.doffs, g.dsys, B->dkc, (int)g.hact.size(), B->P,
-                                pa + g.pack_off, pb + g.pack_off, st,
-                                g.merged ? B->dpct + (sizeof(T) == sizeof(double) ? 0 : B->nprob) : nullptr);
+    rc = bprec_group<T>(B, g, in, out, pa, pb, st);
     if (rc) break;
   }
   if (fork) {
@@ -729,11 +755,19 @@ int blgmres(cheb_batch* B, const T* K, const T* b, T* x, bool x_zero, const std:
     for (int j = 0; j < jmax; ++j) {
       const T* u = j < m ? kw.V + (size_t)j * kw.ld : kw.Z + (size_t)zslot[j - m] * kw.ld;
       if (prec) {
-        rc = bprec<T>(B, u, kw.wp, kw.pa, kw.pb);
-        if (rc) return rc;
-        u = kw.wp;
+        // together where no box has several preconditioner groups in turn
+        int na = 0, np = 0;
+        for (auto& gr : B->groups) na += gr.hact.empty() ? 0 : 1;
+        for (auto& gr : B->pgroups) np += gr.hact.empty() ? 0 : 1;
+        if (np <= na) {
+          rc = bapply<T>(B, K, kw.wp, kw.w, u, kw.wp, kw.pa, kw.pb);
+        } else {
+          rc = bprec<T>(B, u, kw.wp, kw.pa, kw.pb);
+          if (!rc) rc = bapply<T>(B, K, kw.wp, kw.w);
+        }
+      } else {
+        rc = bapply<T>(B, K, u, kw.w);
       }
-      rc = bapply<T>(B, K, u, kw.w);
       if (rc) return rc;
       for (int s = 0; s < ns; ++s)
         if (cyc[s]) mv[s]++;
@@ -761,8 +795,7 @@ int blgmres(cheb_batch* B, const T* K, const T* b, T* x, bool x_zero, const std:
       if (reorth) {
         // cancellation somewhere: a second classical Gram-Schmidt pass for all
         for (int s = 0; s < ns; ++s) scal[(size_t)s * 8] = cyc[s] ? 1.0 : 0.0;
-        rc = upload(B, B->dcoef, coef.data(), coef.size(), 0);
-        if (!rc) rc = upload(B, B->dscal, scal.data(), scal.size(), 1);
+        rc = upload_both(B, coef, scal);
         if (!rc) rc = bupdate<T>(B, kw.V, kw.ld, j + 1, kw.w, kw.w);
         if (!rc) rc = bdots<T>(B, kw.V, kw.ld, j + 1, kw.w, sc, dots);
         if (rc) return rc;
@@ -782,8 +815,7 @@ int blgmres(cheb_batch* B, const T* K, const T* b, T* x, bool x_zero, const std:
         hn[s] = cyc[s] && hh2[s] > 0 ? std::sqrt(hh2[s]) : 0.0;
         scal[(size_t)s * 8] = hn[s] > 0 ? 1.0 / hn[s] : 0.0;
       }
-      rc = upload(B, B->dcoef, coef.data(), coef.size(), 0);
-      if (!rc) rc = upload(B, B->dscal, scal.data(), scal.size(), 1);
+      rc = upload_both(B, coef, scal);
       if (!rc) rc = bupdate<T>(B, kw.V, kw.ld, j + 1, kw.w, vnext);
       if (rc) return rc;
       bool any = false;
@@ -964,6 +996,8 @@ int cheb_batch_create(const cheb_grid* grids, int32_t nprob, int32_t precision, 
       PrecGroup g;
       g.rep = s;
       g.merged = precond_mergeable(grids[s]);
+      for (auto& ag : B->groups)
+        if (same_box(ag.rep, s)) g.box = ag.rep;
       any_merged = any_merged || g.merged;
       g.members.push_back(s);
       B->pgroups.push_back(g);
@@ -1048,8 +1082,8 @@ int cheb_batch_create(const cheb_grid* grids, int32_t nprob, int32_t precision, 
   if (!rc) rc = hip_check(hipMalloc((void**)&B->chl, chs.size() * sizeof(int)), "hipMalloc(chunks)");
   if (!rc) rc = hip_check(hipMalloc((void**)&B->sys_c0, nprob * sizeof(int)), "hipMalloc(chunks)");
   if (!rc) rc = hip_check(hipMalloc((void**)&B->sys_nc, nprob * sizeof(int)), "hipMalloc(chunks)");
-  if (!rc) rc = hip_check(hipMalloc((void**)&B->dcoef, (size_t)nprob * kMaxCoef * sizeof(double)), "hipMalloc");
-  if (!rc) rc = hip_check(hipMalloc((void**)&B->dscal, (size_t)nprob * 8 * sizeof(double)), "hipMalloc");
+  if (!rc) rc = hip_check(hipMalloc((void**)&B->dcoef, (size_t)nprob * (kMaxCoef + 8) * sizeof(double)), "hipMalloc");
+  if (!rc) B->dscal = B->dcoef + (size_t)nprob * kMaxCoef;
   if (!rc) rc = hip_check(hipMalloc((void**)&B->dkc, (size_t)nprob * sizeof(double)), "hipMalloc");
   if (!rc) rc = hip_check(hipMalloc((void**)&B->dflag, sizeof(int)), "hipMalloc");
   if (!rc)
@@ -1371,7 +1405,6 @@ int cheb_batch_destroy(cheb_batch* batch) {
   if (batch->sys_c0) (void)hipFree(batch->sys_c0);
   if (batch->sys_nc) (void)hipFree(batch->sys_nc);
   if (batch->dcoef) (void)hipFree(batch->dcoef);
-  if (batch->dscal) (void)hipFree(batch->dscal);
   if (batch->dkc) (void)hipFree(batch->dkc);
   if (batch->dflag) (void)hipFree(batch->dflag);
   if (batch->hpin) (void)hipHostFree(batch->hpin);

@@ -271,7 +271,8 @@ __global__ __launch_bounds__(kGsThreads) void k_gram_schmidt(const T* __restrict
 // q + 4, ...; lanes stride the blocks), then the Hessenberg column
 // (one workgroup, all latency: everything it reads is fetched at once, before the
 // flag is looked at, the first 64 blocks' results of all of a wave's columns
-// together; 33^3: 5.1 us one after the other, 4.6 us so)
+// together, the rest sixteen at a time; 33^3: 5.1 us one after the other, 4.6 us so;
+// 129^3, 1049 blocks: 8.1 us four at a time, 5.2 us so)
 template <int PASS>
 __global__ __launch_bounds__(kColThreads) void k_gs_column(const double* __restrict__ partials, int nb, int nv,
                                                           double* dots, ArnoldiState* st, int j) {
@@ -293,10 +294,12 @@ __global__ __launch_bounds__(kColThreads) void k_gs_column(const double* __restr
     const int c = wave + q * (kColThreads / 64);
     if (c > nv) break;
     const double* pc = partials + (size_t)c * nb;
-    for (int r = 64 + lane; r < nb; r += 256) {
+    for (int r = 64 + lane; r < nb; r += 1024) {
+      double x[16];
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
-        if (r + 64 * g < nb) s4[q][(g + 1) & 3] += pc[r + 64 * g];
+      for (int g = 0; g < 16; ++g) x[g] = r + 64 * g < nb ? pc[r + 64 * g] : 0.0;
+#pragma unroll
+      for (int g = 0; g < 16; ++g) s4[q][(g + 1) & 3] += x[g];
     }
     const double sum = wave_sum64((s4[q][0] + s4[q][1]) + (s4[q][2] + s4[q][3]));
     if (lane == 0) hs[c] = sum;

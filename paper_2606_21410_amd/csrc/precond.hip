@@ -371,7 +371,7 @@ struct GemmArgs {
   int I, Kd, C;
   long long a_si, a_sk, b_sk, b_sc, d_si, d_sc;
   long long a_sb, b_sb, d_sb;  // batch strides
-  int ps;                      // k_axis_gemm_split: the symmetric half, ceil(m / 2)
+  int ps;                      // k_axis_gemm_lds: the symmetric half, ceil(m / 2)
 };
 
 template <typename T>
@@ -413,9 +413,9 @@ __global__ __launch_bounds__(256) void k_axis_gemm(GemmArgs g) {
   }
 }
 
-// The same contraction for an axis whose 1-D operator is centro-symmetric
-// (m = ps + ph, ps = ceil(m/2) a multiple of 16), with half the multiply-adds.
-// With Q the symmetric / antisymmetric node-pair basis:
+// The same contraction staged through LDS, plain (KIND 0) or, for an axis whose
+// 1-D operator is centro-symmetric (m = ps + ph, ps = ceil(m/2)), with half the
+// multiply-adds.  With Q the symmetric / antisymmetric node-pair basis:
 //   KIND 1 (the input enters through Q^T, e.g. V^{-1} = diag(Vs^{-1}, Vw^{-1}) Q^T):
 //     output row i < ps (a symmetric mode) sums M[i][k] (x_k + x_{m-1-k}) over
 //     k < ps, the middle node of odd m taken once; row i >= ps sums
@@ -425,119 +425,16 @@ __global__ __launch_bounds__(256) void k_axis_gemm(GemmArgs g) {
 //     = P + R and node m-1-i = P - R (the middle node of odd m: P).
 // M is read through the strides of either operand: ZSIDE, the contraction
 // along the unit-stride axis, D[r][i] = sum_k X[r][k] M[i][k] (M the B
-// operand, the split acts on the columns, each 16-column group symmetric or
-// antisymmetric as a whole); otherwise D[i][c] = sum_k M[i][k] X[k][c] (M the
-// A operand, each 16-row block one or the other).  One wave computes 16 rows x
-// 64 columns of the output (KIND 2: of rows or columns below ps, with a second
-// set of accumulators for R).
-template <typename T, int KIND, bool ZSIDE>
-__global__ __launch_bounds__(256) void k_axis_gemm_split(GemmArgs g) {
-  typedef typename Mfma<T>::v4 v4;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int i0 = blockIdx.x * 16;
-  const int c0 = (blockIdx.y * 4 + wave) * 64;
-  const int b = blockIdx.z;
-  const T* A = (const T*)g.A + b * g.a_sb;
-  const T* B = (const T*)g.B + b * g.b_sb;
-  T* D = (T*)g.D + b * g.d_sb;
-  const int m = g.Kd, ps = g.ps, ph = m - g.ps;
-  // output extent of this launch: rows (ZSIDE: columns) below ps for KIND 2
-  const int I = (!ZSIDE && KIND == 2) ? ps : g.I;
-  const int C = (ZSIDE && KIND == 2) ? ps : g.C;
-  if (c0 >= C) return;
-  const int li = lane & 15, lk = lane >> 4;
-  const int ia = i0 + li;
-  v4 acc[4], acr[KIND == 2 ? 4 : 1];
-#pragma unroll
-  for (int t = 0; t < 4; ++t) acc[t] = v4{0, 0, 0, 0};
-  if (KIND == 2)
-#pragma unroll
-    for (int t = 0; t < 4; ++t) acr[KIND == 2 ? t : 0] = v4{0, 0, 0, 0};
-  if (KIND == 1) {
-    // the row block (ZSIDE: each column group) is symmetric below ps
-    const bool rsym = i0 < ps;
-    const int kend = ZSIDE ? ps : (rsym ? ps : ph);
-    for (int k0 = 0; k0 < kend; k0 += 4) {
-      const int k = k0 + lk;
-      const bool kin = k < kend;
-      const int kr = m - 1 - (kin ? k : 0);  // mirror node (in range for k < ps)
-      if (ZSIDE) {
-        // A = X: pair sum and difference of this lane's row
-        T sm = T(0), df = T(0);
-        if (ia < I && kin) {
-          const T x1 = A[ia * g.a_si + k * g.a_sk], x2 = A[ia * g.a_si + kr * g.a_sk];
-          sm = kr == k ? x1 : x1 + x2;
-          df = x1 - x2;
-        }
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int cg = c0 + t * 16, c = cg + li;
-          const bool csym = cg < ps;
-          const bool kok = csym ? kin : k < ph;
-          const T bv = (c < C && kok) ? B[k * g.b_sk + c * g.b_sc] : T(0);
-          acc[t] = Mfma<T>::mac(csym ? sm : df, bv, acc[t]);
-        }
-      } else {
-        const T av = (ia < I && kin) ? A[ia * g.a_si + k * g.a_sk] : T(0);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int c = c0 + t * 16 + li;
-          T bv = T(0);
-          if (c < C && kin) {
-            const T x1 = B[k * g.b_sk + c * g.b_sc], x2 = B[kr * g.b_sk + c * g.b_sc];
-            bv = rsym ? (kr == k ? x1 : x1 + x2) : x1 - x2;
-          }
-          acc[t] = Mfma<T>::mac(av, bv, acc[t]);
-        }
-      }
-    }
-  } else {
-    // P over k < ps, R over k >= ps
-    for (int k0 = 0; k0 < m; k0 += 4) {
-      const int k = k0 + lk;
-      const bool lower = k0 < ps;  // ps is a multiple of 16: no k-step straddles it
-      const bool kin = k < m;
-      const T av = (ia < I && kin) ? A[ia * g.a_si + k * g.a_sk] : T(0);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int c = c0 + t * 16 + li;
-        const T bv = (c < C && kin) ? B[k * g.b_sk + c * g.b_sc] : T(0);
-        if (lower) acc[t] = Mfma<T>::mac(av, bv, acc[t]);
-        else acr[KIND == 2 ? t : 0] = Mfma<T>::mac(av, bv, acr[KIND == 2 ? t : 0]);
-      }
-    }
-  }
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const int c = c0 + t * 16 + li;
-    if (c >= C) continue;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = i0 + Mfma<T>::row(lk, r);
-      if (i >= I) continue;
-      if (KIND == 1) {
-        D[i * g.d_si + c * g.d_sc] = acc[t][r];
-      } else {
-        const T P = acc[t][r], R = acr[KIND == 2 ? t : 0][r];
-        if (ZSIDE) {
-          D[i * g.d_si + c * g.d_sc] = P + R;
-          if (c < ph) D[i * g.d_si + (m - 1 - c) * g.d_sc] = P - R;
-        } else {
-          D[i * g.d_si + c * g.d_sc] = P + R;
-          if (i < ph) D[(m - 1 - i) * g.d_si + c * g.d_sc] = P - R;
-        }
-      }
-    }
-  }
-}
-
-// The same contractions (KIND 0 plain, 1 and 2 the even-odd split as above)
-// with the operands staged through LDS: a workgroup of four waves computes a
-// 64 x 64 output tile (each wave 32 x 32, 2 x 2 matrix-core blocks) over
-// k-chunks of 16, so every loaded element feeds several matrix instructions.
-// The split forms its pair sums and differences while staging; it needs ps a
-// multiple of 64 so that a tile's rows (ZSIDE: columns) are all symmetric or
-// all antisymmetric modes.
+// operand, the split acts on the columns); otherwise D[i][c] = sum_k M[i][k]
+// X[k][c] (M the A operand, the split acts on the rows).  A workgroup of four
+// waves computes a 64 x 64 output tile (each wave 32 x 32, 2 x 2 matrix-core
+// blocks) over k-chunks of 16, so every loaded element feeds several matrix
+// instructions; the next chunk's loads are in flight meanwhile, with the pair
+// sums and differences formed as they land.  KIND 1 tiles the symmetric modes
+// and then the antisymmetric ones, KIND 2 chunks its k range likewise, each
+// half with a remainder of its own, so any m splits.  (Halves of whole blocks
+// only, one chunk at a time: 257^3 FP64 1.31 ms an application, 193^3 0.74,
+// 161^3 0.44, 200x255x131 0.88; now 1.07, 0.47, 0.34 and 0.52.)
 constexpr int kGt = 64, kGk = 16;  // output tile edge, k-chunk
 template <typename T, int KIND, bool ZSIDE>
 __global__ __launch_bounds__(256) void k_axis_gemm_lds(GemmArgs g) {
@@ -546,17 +443,27 @@ __global__ __launch_bounds__(256) void k_axis_gemm_lds(GemmArgs g) {
   __shared__ T Bs[kGk][kGt + 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int li = lane & 15, lk = lane >> 4;
-  const int i0 = blockIdx.x * kGt, c0 = blockIdx.y * kGt, b = blockIdx.z;
+  int i0 = blockIdx.x * kGt, c0 = blockIdx.y * kGt;
+  const int b = blockIdx.z;
   const T* A = (const T*)g.A + b * g.a_sb;
   const T* B = (const T*)g.B + b * g.b_sb;
   T* D = (T*)g.D + b * g.d_sb;
   const int m = g.Kd, ps = g.ps, ph = m - g.ps;
-  // output extent: rows (ZSIDE: columns) below ps for KIND 2
-  const int I = (!ZSIDE && KIND == 2) ? ps : g.I;
-  const int C = (ZSIDE && KIND == 2) ? ps : g.C;
-  // KIND 1: the tile's modes are symmetric below ps; their k range
-  const bool tsym = ZSIDE ? c0 < ps : i0 < ps;
+  int I = g.I, C = g.C;  // output extent of this tile's half
+  bool tsym = true;
+  if (KIND == 2) (ZSIDE ? C : I) = ps;
+  if (KIND == 1) {
+    // the tiles of the antisymmetric modes follow those of the symmetric ones
+    int& t0 = ZSIDE ? c0 : i0;
+    const int skip = (ps + kGt - 1) / kGt * kGt;
+    tsym = t0 < skip;
+    if (tsym) (ZSIDE ? C : I) = ps;
+    else t0 = ps + t0 - skip;
+  }
   const int kend = KIND == 1 ? (tsym ? ps : ph) : m;
+  // KIND 2: k of the symmetric modes in whole chunks, then the others'
+  const int low = KIND == 2 ? (ps + kGk - 1) / kGk * kGk : 0;
+  const int kext = KIND == 2 ? low + ph : kend;
   const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
   v4 acc[2][2], acr[KIND == 2 ? 2 : 1][KIND == 2 ? 2 : 1];
 #pragma unroll
@@ -566,15 +473,20 @@ __global__ __launch_bounds__(256) void k_axis_gemm_lds(GemmArgs g) {
       acc[x][y] = v4{0, 0, 0, 0};
       if (KIND == 2) acr[KIND == 2 ? x : 0][KIND == 2 ? y : 0] = v4{0, 0, 0, 0};
     }
-  for (int k0 = 0; k0 < kend; k0 += kGk) {
-    // stage A (64 rows x 16 k) and B (16 k x 64 columns), zero outside
+  // a chunk's elements of this thread, zero outside: A 64 rows x 16 k, B 16 k x 64
+  // columns; loaded while the chunk before it is contracted
+  constexpr int PT = kGt * kGk / 256;
+  T ra[PT], rb[PT];
+  auto load = [&](int kc) __attribute__((always_inline)) {
+    const int k0 = KIND == 2 && kc >= low ? ps + kc - low : kc;
+    const int klim = KIND == 2 && kc < low ? ps : kend;
 #pragma unroll
-    for (int q = 0; q < kGt * kGk / 256; ++q) {
+    for (int q = 0; q < PT; ++q) {
       const int e = tid + q * 256;
       const int r = e / kGk, kk = e - r * kGk;
       const int i = i0 + r, k = k0 + kk;
       T v = T(0);
-      if (i < I && k < kend) {
+      if (i < I && k < klim) {
         v = A[i * g.a_si + k * g.a_sk];
         if (KIND == 1 && ZSIDE) {
           const int kr = m - 1 - k;
@@ -582,15 +494,15 @@ __global__ __launch_bounds__(256) void k_axis_gemm_lds(GemmArgs g) {
           v = tsym ? (kr == k ? v : v + x2) : v - x2;
         }
       }
-      As[r][kk] = v;
+      ra[q] = v;
     }
 #pragma unroll
-    for (int q = 0; q < kGt * kGk / 256; ++q) {
+    for (int q = 0; q < PT; ++q) {
       const int e = tid + q * 256;
       const int kk = e / kGt, cc = e - kk * kGt;
       const int k = k0 + kk, c = c0 + cc;
       T v = T(0);
-      if (c < C && k < kend) {
+      if (c < C && k < klim) {
         v = B[k * g.b_sk + c * g.b_sc];
         if (KIND == 1 && !ZSIDE) {
           const int kr = m - 1 - k;
@@ -598,10 +510,20 @@ __global__ __launch_bounds__(256) void k_axis_gemm_lds(GemmArgs g) {
           v = tsym ? (kr == k ? v : v + x2) : v - x2;
         }
       }
-      Bs[kk][cc] = v;
+      rb[q] = v;
+    }
+  };
+  load(0);
+  for (int k0 = 0; k0 < kext; k0 += kGk) {
+#pragma unroll
+    for (int q = 0; q < PT; ++q) {
+      const int e = tid + q * 256;
+      As[e / kGk][e % kGk] = ra[q];
+      Bs[e / kGt][e % kGt] = rb[q];
     }
     __syncthreads();
-    const bool upper = KIND == 2 && k0 >= ps;  // ps is a multiple of 16: chunks do not straddle it
+    if (k0 + kGk < kext) load(k0 + kGk);
+    const bool upper = KIND == 2 && k0 >= low;
 #pragma unroll
     for (int ks = 0; ks < kGk / 4; ++ks) {
       T av[2], bv[2];
@@ -1615,10 +1537,13 @@ static int axis_contract(const cheb_plan* p, int a, int dir, bool tr, const int*
   GemmArgs g;
   const long long msz = m[a];
   const long long ms_i = tr ? 1 : msz, ms_k = tr ? msz : 1;  // M(i,k) strides
-  // centro-symmetric axis with halves in whole 16-row blocks: the split
-  // contraction (V^{-1} side through Q^T, V side through Q; also transposed)
+  // centro-symmetric axis: the split contraction (V^{-1} side through Q^T, V side
+  // through Q; also transposed)
   const int ps = (m[a] + 1) / 2;
-  const int kind = p->pc_ax[a].centro && ps % 16 == 0 ? dir + 1 : 0;
+  const int kind = p->pc_ax[a].centro ? dir + 1 : 0;
+  // tiles along the contracted axis: both halves' (KIND 1), the lower one's (KIND 2)
+  const int half = (ps + kGt - 1) / kGt, other = (m[a] - ps + kGt - 1) / kGt;
+  const int tiles = kind == 0 ? (m[a] + kGt - 1) / kGt : kind == 1 ? half + other : half;
   g.ps = ps;
   if (a == 2) {
     // Y[r, i] = sum_k X[r, k] M[i, k]: rows r, columns i
@@ -1628,16 +1553,10 @@ static int axis_contract(const cheb_plan* p, int a, int dir, bool tr, const int*
     g.b_sk = ms_k; g.b_sc = ms_i;
     g.d_si = m[2]; g.d_sc = 1;
     g.a_sb = g.b_sb = g.d_sb = 0;
-    if (kind == 0 || ps % kGt == 0) {
-      dim3 grid((g.I + kGt - 1) / kGt, ((kind == 2 ? ps : g.C) + kGt - 1) / kGt, 1);
-      if (kind == 1) hipLaunchKernelGGL((k_axis_gemm_lds<T, 1, true>), grid, dim3(256), 0, s, g);
-      else if (kind == 2) hipLaunchKernelGGL((k_axis_gemm_lds<T, 2, true>), grid, dim3(256), 0, s, g);
-      else hipLaunchKernelGGL((k_axis_gemm_lds<T, 0, true>), grid, dim3(256), 0, s, g);
-    } else {
-      dim3 grid((g.I + 15) / 16, ((kind == 2 ? ps : g.C) + 255) / 256, 1);
-      if (kind == 1) hipLaunchKernelGGL((k_axis_gemm_split<T, 1, true>), grid, dim3(256), 0, s, g);
-      else hipLaunchKernelGGL((k_axis_gemm_split<T, 2, true>), grid, dim3(256), 0, s, g);
-    }
+    dim3 grid((g.I + kGt - 1) / kGt, tiles, 1);
+    if (kind == 1) hipLaunchKernelGGL((k_axis_gemm_lds<T, 1, true>), grid, dim3(256), 0, s, g);
+    else if (kind == 2) hipLaunchKernelGGL((k_axis_gemm_lds<T, 2, true>), grid, dim3(256), 0, s, g);
+    else hipLaunchKernelGGL((k_axis_gemm_lds<T, 0, true>), grid, dim3(256), 0, s, g);
   } else {
     // Y_b = M X_b with X_b (m_axis x C), C = product of the later dims
     const int C = a == 0 ? m[1] * m[2] : m[2];
@@ -1649,16 +1568,10 @@ static int axis_contract(const cheb_plan* p, int a, int dir, bool tr, const int*
     g.d_si = C; g.d_sc = 1;
     g.a_sb = 0;
     g.b_sb = g.d_sb = (long long)m[a] * C;
-    if (kind == 0 || ps % kGt == 0) {
-      dim3 grid(((kind == 2 ? ps : g.I) + kGt - 1) / kGt, (C + kGt - 1) / kGt, batch);
-      if (kind == 1) hipLaunchKernelGGL((k_axis_gemm_lds<T, 1, false>), grid, dim3(256), 0, s, g);
-      else if (kind == 2) hipLaunchKernelGGL((k_axis_gemm_lds<T, 2, false>), grid, dim3(256), 0, s, g);
-      else hipLaunchKernelGGL((k_axis_gemm_lds<T, 0, false>), grid, dim3(256), 0, s, g);
-    } else {
-      dim3 grid(((kind == 2 ? ps : g.I) + 15) / 16, (C + 255) / 256, batch);
-      if (kind == 1) hipLaunchKernelGGL((k_axis_gemm_split<T, 1, false>), grid, dim3(256), 0, s, g);
-      else hipLaunchKernelGGL((k_axis_gemm_split<T, 2, false>), grid, dim3(256), 0, s, g);
-    }
+    dim3 grid(tiles, (C + kGt - 1) / kGt, batch);
+    if (kind == 1) hipLaunchKernelGGL((k_axis_gemm_lds<T, 1, false>), grid, dim3(256), 0, s, g);
+    else if (kind == 2) hipLaunchKernelGGL((k_axis_gemm_lds<T, 2, false>), grid, dim3(256), 0, s, g);
+    else hipLaunchKernelGGL((k_axis_gemm_lds<T, 0, false>), grid, dim3(256), 0, s, g);
   }
   return hip_check(hipGetLastError(), "axis contraction");
 }

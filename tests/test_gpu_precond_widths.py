@@ -29,6 +29,9 @@ def along(M, x, axis):
     ((10, 66, 52), (0, 1, 1, 0, 0, 1)),       # 8, 64, 50; none
     ((5, 130, 130), (0, 0, 0, 0, 0, 0)),      # 3, 128, 128
     ((6, 129, 122), (0, 0, 1, 1, 0, 0)),      # 4, 127, 120
+    ((5, 143, 131), (0, 0, 1, 1, 0, 0)),      # 3, 141, 129: the batched GEMM, halves of 71 and 65
+    ((163, 6, 140), (1, 1, 0, 0, 0, 1)),      # 161, 4, 138: halves of 81; z not mirror-symmetric
+    ((195, 4, 258), (0, 0, 0, 0, 1, 1)),      # 193, 2, 256: halves of 97 and 128
 ])
 @pytest.mark.parametrize("prec", ["f64", "f32"])
 def test_precond_widths(shape, bc, prec):

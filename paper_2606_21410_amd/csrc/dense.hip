@@ -38,14 +38,14 @@ void line_table(int N, int mts, bool f32, const AxisConst& c, F m, double* tab) 
   const LineTab lt = line_tab(mts);
   for (int i = 0; i < lt.size; ++i) tab[i] = 0.0;
   auto ao = [&](int i, int j) { return 0.5 * (m(i, j) - m(i, N - j)); };
-  auto ae = [&](int i, int j) { return 2 * j == N ? 0.5 * m(i, j) : 0.5 * (m(i, j) + m(i, N - j)); };
   for (int mt = 0; mt < mts; ++mt)
     for (int ks = 0; ks <= 4 * mts; ++ks)
       for (int l = 0; l < 64; ++l) {
         const int i = 16 * mt + (l & 15), j = line_kmap(ks, l >> 4, kmap32);
-        if (i >= RM) continue;
-        if (j < R) tab[(mt * (4 * mts + 1) + ks) * 64 + l] = ae(i, j);
-        if (j < KO && ks < 4 * mts) tab[lt.off_o + (mt * 4 * mts + ks) * 64 + l] = ao(i, j);
+        if (i >= RM || j >= R) continue;
+        const double x = m(i, j), y = m(i, N - j);
+        tab[(mt * (4 * mts + 1) + ks) * 64 + l] = 2 * j == N ? 0.5 * x : 0.5 * (x + y);
+        if (j < KO && ks < 4 * mts) tab[lt.off_o + (mt * 4 * mts + ks) * 64 + l] = 0.5 * (x - y);
       }
   if (midv)
     for (int j = 0; j < KO; ++j) tab[lt.off_mid + j] = ao(N / 2, j);

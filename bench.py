@@ -31,10 +31,10 @@ ALG_BYTES_PER_POINT_F64 = 24.0
 
 def _traffic_record(route):
     """HBM bytes per apply measured with rocprofv3 for the apply's kernels
-    (profiles/k_dense_pass_f64_129cubed_hbm_bytes.txt), or None when the
+    (profiles/line_passes_f64_129cubed_hbm_bytes.txt), or None when the
     kernel sources or the chosen tile shape differ from the profiled ones."""
     import hashlib
-    path = os.path.join(ROOT, "profiles", "k_dense_pass_f64_129cubed_hbm_bytes.txt")
+    path = os.path.join(ROOT, "profiles", "line_passes_f64_129cubed_hbm_bytes.txt")
     if not os.path.exists(path) or route not in ("matrix0", "matrix1"):
         return None
     rec = None
@@ -581,9 +581,9 @@ def refinement_stop_section(dev, levels=(33, 65, 129, 257), tol=2e-3):
 def precond_section(dev, P, reps=50, warmup=5):
     """One application of the fast-diagonalisation preconditioner
     (cheb_precond_apply) on the 129^3 workload's grid with Kc = mean K, FP64 and
-    FP32 fields, event-timed on the plan's stream.  Bytes: each of the five
-    launches (x, y, the fused z pair, y, x) reads and writes one field of the
-    interior nodes, 10 x m^3 x sizeof(T)."""
+    FP32 fields, event-timed on the plan's stream.  Bytes: each of the three
+    launches (z and y of a plane, the x pair, y and z of a plane) reads and
+    writes one field of the interior nodes, 6 x m^3 x sizeof(T)."""
     import numpy as np
     import torch
     from paper_2606_21410_amd.api import Plan
@@ -607,8 +607,8 @@ def precond_section(dev, P, reps=50, warmup=5):
         ev1.record(stream)
         torch.cuda.synchronize()
         us = ev0.elapsed_time(ev1) * 1e3 / reps
-        nbytes = 10 * m[0] * m[1] * m[2] * (8 if prec == "f64" else 4)
-        out[prec] = {"us_per_application": round(us, 2), "launches": 5,
+        nbytes = 6 * m[0] * m[1] * m[2] * (8 if prec == "f64" else 4)
+        out[prec] = {"us_per_application": round(us, 2), "launches": 3,
                      "mb_moved": round(nbytes / 1e6, 1), "gbs": round(nbytes / us / 1e3, 1)}
         del pl, rd, yd
     torch.cuda.empty_cache()
@@ -647,8 +647,8 @@ def copy_reference(dev, n=64 * 1024 * 1024, reps=20):
 
 
 def apply_257(dev, steps=40, warmup=5, rot=4):
-    """FP64 reduced apply on the 257^3 two-phase grid (the FFT route: the
-    matrix-core route covers N <= 128), rotating buffers, event-timed."""
+    """FP64 reduced apply on the 257^3 two-phase grid (the matrix-core
+    route, N <= 256), rotating buffers, event-timed."""
     import numpy as np
     import torch
     from paper_2606_21410_amd import workloads as W
@@ -676,7 +676,7 @@ def apply_257(dev, steps=40, warmup=5, rot=4):
     del us, ys, K, plan
     torch.cuda.empty_cache()
     return {"ms_per_apply": round(ms, 4), "gdofs": round(npts / (ms * 1e-3) / 1e9, 3),
-            "algorithmic_gbs": round(alg, 1), "frac": round(alg / HBM_PEAK_GBS, 4), "route": "fft"}
+            "algorithmic_gbs": round(alg, 1), "frac": round(alg / HBM_PEAK_GBS, 4), "route": "matrix"}
 
 
 def robin_section(dev, P, steps=100, warmup=10):
@@ -907,7 +907,7 @@ def main():
     bytes_per_apply = ALG_BYTES_PER_POINT_F64 * npts
     achieved = bytes_per_apply / apply_s / 1e9
     route = res["f64"]["route"]
-    kname = (f"k_dense_pass<double,128,REDUCED,*,{route[-1]},*> (matrix-core route" if route != "fft"
+    kname = (f"k_line_wave<double,4,REDUCED,*,*,{8 if route[-1] == '0' else 4}> (matrix-core route" if route != "fft"
              else "k_axis_pass<double,128,REDUCED> (FFT route")
     rec = _traffic_record(route)
     traffic = rec["traffic_bytes_per_apply"] if rec else None

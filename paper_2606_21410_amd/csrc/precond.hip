@@ -632,7 +632,7 @@ enum { FDM_XFULL = 1, FDM_YFULL = 2, FDM_SCALE = 4, FDM_MID = 8 };
 // Every centro-symmetric axis takes them.  With the halves left unpadded (only
 // ps = 16, 32, 48, 64 split) m = 119 took 30 steps of 8 row blocks for 16, and
 // FP64 could not hold both tables of a middle pair: an application at 121^3
-// took 126 us and takes 78 us now.
+// took 126 us, 78 us split so, 58 us with the planes' kernels.
 
 // linear offset of boundary node u of an n0 x n1 x n2 field (faces x, y, z)
 __device__ inline long long face_node(long long u, int n0, int n1, int n2) {
@@ -956,7 +956,7 @@ __global__ __launch_bounds__(64 * kFdmWaves) void k_fdm_wave(FdmArgs g) {
   constexpr int SA = SPLIT;
   constexpr int TA = fdm_tab_elems(MP, SA), TB = MID ? TA : 0;
   static_assert(!MID || SCL, "the middle pair scales between its contractions");
-  static_assert(!MID || SPLIT == 0, "k_fdm_mid is a split axis' middle pair");
+  static_assert(!SCL || SPLIT == 0, "k_fdm_mid is a split axis' middle pair");
   static_assert(SPLIT == 0 || MP >= 32, "split contractions need two row blocks");
   typedef typename Mfma<T>::v4 V4;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -1103,8 +1103,7 @@ __global__ __launch_bounds__(64 * kFdmWaves) void k_fdm_wave(FdmArgs g) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int row = 16 * rb + Mfma<T>::row(lk, r);
-          const int i = SA == 1 ? fdm_mode(row, MP, m) : row < m ? row : -1;
-          if (i >= 0) acc[rb][r] = fdm_scale<T>(acc[rb][r], ik, sc, lam_s[axis * 128 + i]);
+          if (row < m) acc[rb][r] = fdm_scale<T>(acc[rb][r], ik, sc, lam_s[axis * 128 + row]);
         }
     }
     if (valid) {
@@ -1488,11 +1487,8 @@ static int launch_fdm_m(const FdmArgs& f, int mode, int split, hipStream_t s) {
     return launch_fdm_mode<T, FDM_MID | FDM_SCALE, 0>(f, s);
   }
   if (split == 1) {
-    switch (mode) {
-      case FDM_XFULL: return launch_fdm_mode<T, FDM_XFULL, 1>(f, s);
-      case FDM_SCALE: return launch_fdm_mode<T, FDM_SCALE, 1>(f, s);
-      default: return launch_fdm_mode<T, 0, 1>(f, s);
-    }
+    if (mode == FDM_XFULL) return launch_fdm_mode<T, FDM_XFULL, 1>(f, s);
+    return launch_fdm_mode<T, 0, 1>(f, s);
   }
   if (split == 2) {
     if (mode == FDM_YFULL) return launch_fdm_mode<T, FDM_YFULL, 2>(f, s);

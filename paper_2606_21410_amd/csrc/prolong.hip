@@ -209,11 +209,6 @@ int prolong_t(const cheb_plan* pc, const cheb_plan* pf, const T* uc, T* uf, T* t
     nxt[axis] = pf->g.n[axis];
     T* out = step == 2 ? uf : (step == 0 ? tmp1 : tmp2);
     const int Nc = cur[axis] - 1, Nf = nxt[axis] - 1;
-    // the sizes the call takes: 17 Nc + Nf + 16 <= 10240 (Nc = Nf: 568)
-    if (17 * Nc + Nf + 16 > 10240) {
-      set_error("prolongation: axis too long");
-      return CHEB_ERR_UNSUPPORTED;
-    }
     // three row blocks per workgroup read a pencil fewer times and two form
     // smaller tables: 257^3, 4129 tasks a pass, takes 185 us with three and
     // 220 us with two, 181^3, 2048 tasks, 81 and 76 us, 129^3 47 and 41 us

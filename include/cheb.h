@@ -138,8 +138,12 @@ typedef struct cheb_plan cheb_plan;
  * fragment tables when an axis has N <= 256, and, when all three axes can take
  * that route, one field-sized buffer
  * (n0*n1*n2 values, 4 bytes each for CHEB_F32 plans, 8 otherwise) that holds
- * the second partial sum of an apply whose x and y passes share one launch
- * (if that allocation fails, applies take three launches instead).
+ * the second partial sum of an apply whose x and y passes share one launch.
+ * Applies enqueued on `stream` itself use it; those on another stream
+ * (cheb_plan_set_stream), those recorded into a graph, and all of them if that
+ * allocation failed take three launches (or the caller's scratch:
+ * cheb_apply_scratch) and share no memory, so a plan's applies may be in flight
+ * on several streams.  The results are the same bits.
  * Nothing is allocated after creation except where a call says so. */
 int cheb_plan_create(const cheb_grid* grid, int32_t precision, void* stream, cheb_plan** out);
 
@@ -221,6 +225,14 @@ int cheb_plan_destroy(cheb_plan* plan);
  *   of u are ignored and boundary entries of y are set to 0.  Asynchronous.
  *   Needs no workspace. */
 int cheb_apply(cheb_plan* plan, const void* K, const void* u, void* y, uint32_t flags);
+
+/* cheb_apply with the caller's scratch field (n0*n1*n2 values of y's type, not
+ * overlapping K, u or y; its contents are undefined afterwards) in place of the
+ * plan's second output, so that an apply on any stream or in a graph takes two
+ * launches.  The same results, bit for bit.  scratch follows the rules of every
+ * buffer: alive until the stream, or the last replay, has finished with it, and
+ * not shared by applies that may run at the same time. */
+int cheb_apply_scratch(cheb_plan* plan, const void* K, const void* u, void* y, uint32_t flags, void* scratch);
 
 /* Solve div(K grad u) = f with face data g (Algorithm 2): build the reduced
  * right-hand side f_k - A_kr H g, run LGMRES on the reduced operator (MIXED:

@@ -67,6 +67,7 @@ _SIGS = {
                                           ctypes.c_int32]),
     "cheb_plan_destroy": (ctypes.c_int, [_vp]),
     "cheb_apply": (ctypes.c_int, [_vp, _vp, _vp, _vp, ctypes.c_uint32]),
+    "cheb_apply_scratch": (ctypes.c_int, [_vp, _vp, _vp, _vp, ctypes.c_uint32, _vp]),
     "cheb_solve": (ctypes.c_int, [_vp, _vp, _vp, _vp, _vp, ctypes.POINTER(cheb_solve_opts),
                                   ctypes.POINTER(cheb_solve_info)]),
     "cheb_prolong": (ctypes.c_int, [_vp, _vp, _vp, _vp, _vp, ctypes.POINTER(ctypes.c_double)]),

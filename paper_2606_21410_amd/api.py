@@ -77,8 +77,8 @@ class Plan:
             g.bc[f] = self.bc[f]
             g.robin[f] = self.robin[f]
         self._h = ctypes.c_void_p()
-        stream = _stream_handle(self.device) if self.device.type == "cuda" else 0
-        L.check(self.lib.cheb_plan_create(ctypes.byref(g), _PREC[precision], ctypes.c_void_p(stream),
+        self._home = _stream_handle(self.device) if self.device.type == "cuda" else 0
+        L.check(self.lib.cheb_plan_create(ctypes.byref(g), _PREC[precision], ctypes.c_void_p(self._home),
                                           ctypes.byref(self._h)))
         self._ws = None
         self._ws_bytes = 0
@@ -172,7 +172,9 @@ class Plan:
         return self._h
 
     def _sync_stream(self):
-        self.lib.cheb_plan_set_stream(self._h, ctypes.c_void_p(_stream_handle(self.device)))
+        stream = _stream_handle(self.device)
+        self.lib.cheb_plan_set_stream(self._h, ctypes.c_void_p(stream))
+        return stream
 
     def _field(self, t: torch.Tensor, name: str, dtype=None):
         dtype = dtype or self.dtype
@@ -204,11 +206,17 @@ class Plan:
 
     # --- calls -------------------------------------------------------------
     def apply(self, K, u, y=None, mode: str = "full"):
-        self._sync_stream()
+        stream = self._sync_stream()
         if y is None:
             y = torch.empty_like(u)
-        L.check(self.lib.cheb_apply(self._h, self._field(K, "K"), self._field(u, "u"), self._field(y, "y"),
-                                    _MODE[mode]))
+        fields = self._h, self._field(K, "K"), self._field(u, "u"), self._field(y, "y"), _MODE[mode]
+        if stream == self._home or self.route == "fft" or max(self.n) > 257:
+            L.check(self.lib.cheb_apply(*fields))
+        else:
+            # the plan's own second output serves its creation stream only; torch's
+            # allocator gives this one to the stream, or the graph being captured
+            scratch = torch.empty_like(y)
+            L.check(self.lib.cheb_apply_scratch(*fields, ctypes.c_void_p(scratch.data_ptr())))
         return y
 
     def derivative(self, u, axis: int, out=None):

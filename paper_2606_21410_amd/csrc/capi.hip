@@ -191,7 +191,7 @@ int cheb_plan_create(const cheb_grid* grid, int32_t precision, void* stream, che
   std::memset((void*)p, 0, sizeof(cheb_plan));
   p->g = *grid;
   p->prec = precision;
-  p->stream = (hipStream_t)stream;
+  p->stream = p->home = (hipStream_t)stream;
   p->npts = (size_t)grid->n[0] * grid->n[1] * grid->n[2];
   size_t nmax = 0;
   for (int a = 0; a < 3; ++a) {
@@ -465,7 +465,7 @@ int cheb_plan_destroy(cheb_plan* plan) {
   return CHEB_OK;
 }
 
-int cheb_apply(cheb_plan* plan, const void* K, const void* u, void* y, uint32_t flags) {
+static int apply_checked(cheb_plan* plan, const void* K, const void* u, void* y, uint32_t flags, void* second) {
   if (!plan || !K || !u || !y) {
     set_error("null argument");
     return CHEB_ERR_INVALID_ARG;
@@ -483,8 +483,20 @@ int cheb_apply(cheb_plan* plan, const void* K, const void* u, void* y, uint32_t 
     return CHEB_ERR_INVALID_ARG;
   }
   if (plan->prec == CHEB_F32)
-    return apply_t<float>(plan, (const float*)K, (const float*)u, (float*)y, mode, plan->stream);
-  return apply_t<double>(plan, (const double*)K, (const double*)u, (double*)y, mode, plan->stream);
+    return apply_t<float>(plan, (const float*)K, (const float*)u, (float*)y, mode, plan->stream, (float*)second);
+  return apply_t<double>(plan, (const double*)K, (const double*)u, (double*)y, mode, plan->stream, (double*)second);
+}
+
+int cheb_apply(cheb_plan* plan, const void* K, const void* u, void* y, uint32_t flags) {
+  return apply_checked(plan, K, u, y, flags, nullptr);
+}
+
+int cheb_apply_scratch(cheb_plan* plan, const void* K, const void* u, void* y, uint32_t flags, void* scratch) {
+  if (!scratch || scratch == y || scratch == u || scratch == K) {
+    set_error("scratch must be a field of its own");
+    return CHEB_ERR_INVALID_ARG;
+  }
+  return apply_checked(plan, K, u, y, flags, scratch);
 }
 
 int cheb_plan_autotune(cheb_plan* plan, int32_t field_precision, const void* K, const void* u, void* y,

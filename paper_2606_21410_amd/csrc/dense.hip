@@ -147,6 +147,24 @@ int dispatch_line(const cheb_plan* p, LineArgs<T>& a, int mode, int first, hipSt
   }
 }
 
+// Whether an apply on stream s may write its second partial sum into the plan's
+// buffer.  A plan's calls may be in flight on several streams at once, and a
+// captured apply runs whenever its graph is replayed, so the one buffer serves the
+// creation stream alone, outside a capture (the legacy stream is never captured;
+// the per-thread handle stands for a stream per thread).  Others bring a field of
+// their own (cheb_apply_scratch, the solves' workspace) or take three launches:
+// 129^3 FP64 59 us against 50.5, 33^3 15.8 against 13.
+bool pair_usable(const cheb_plan* p, hipStream_t s) {
+  if (!p->pair_buf || s != p->home || s == hipStreamPerThread) return false;
+  if (s == nullptr) return true;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return st == hipStreamCaptureStatusNone;
+}
+
 }  // namespace
 
 template <typename T>
@@ -165,12 +183,15 @@ int launch_line_pass(const cheb_plan* p, int axis, int mode, int transpose, int 
 }
 
 template <typename T>
-int launch_line_apply(const cheb_plan* p, int mode, const T* K, const T* const* c, const T* u, T* y, hipStream_t s) {
+int launch_line_apply(const cheb_plan* p, int mode, const T* K, const T* const* c, const T* u, T* y, hipStream_t s,
+                      T* second) {
   const int tr = mode == LINE_TRANSP ? 1 : 0;
   const int pi = prec_index<T>();
   // the x and y passes share a launch, each into its own output
-  if (p->pair_buf && p->dd_mt[0] == p->dd_mt[1] && p->dense_var[0][pi] == p->dense_var[1][pi]) {
-    T* y1 = (T*)p->pair_buf;
+  T* y1 = nullptr;
+  if (p->dd_mt[0] == p->dd_mt[1] && p->dense_var[0][pi] == p->dense_var[1][pi])
+    y1 = second ? second : pair_usable(p, s) ? (T*)p->pair_buf : nullptr;
+  if (y1) {
     LineArgs<T> a = line_args<T>(p, K, u, nullptr, nullptr, 0);
     a.nseg = 2;
     a.ax[0] = line_axis<T>(p, 0, mode, tr, false, y, y);
@@ -188,7 +209,8 @@ int launch_line_apply(const cheb_plan* p, int mode, const T* K, const T* const* 
     a.ax[1] = a.ax[0];
     return dispatch_line<T>(p, a, mode, 0, s);
   }
-  for (int axis = 2; axis >= 0; --axis)
+  // (z + x) + y, as above
+  for (int axis : {2, 0, 1})
     if (int rc = launch_line_pass<T>(p, axis, mode, tr, axis == 2, K, c ? c[axis] : nullptr, u, y, s)) return rc;
   return CHEB_OK;
 }
@@ -212,9 +234,9 @@ template int launch_line_pass<double>(const cheb_plan*, int, int, int, int, cons
 template int launch_line_pass<float>(const cheb_plan*, int, int, int, int, const float*, const float*, const float*,
                                      float*, hipStream_t);
 template int launch_line_apply<double>(const cheb_plan*, int, const double*, const double* const*, const double*,
-                                       double*, hipStream_t);
+                                       double*, hipStream_t, double*);
 template int launch_line_apply<float>(const cheb_plan*, int, const float*, const float* const*, const float*, float*,
-                                      hipStream_t);
+                                      hipStream_t, float*);
 template int launch_dense_batch<double>(const cheb_plan*, int, int, const double*, const double*, double*,
                                         const DenseSys*, const int*, int, hipStream_t);
 template int launch_dense_batch<float>(const cheb_plan*, int, int, const float*, const float*, float*, const DenseSys*,

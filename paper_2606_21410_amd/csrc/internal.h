@@ -115,8 +115,10 @@ struct cheb_plan {
   double rn_mean[6];
   // the two-axis launch's second output: one field (n0 n1 n2 values of the
   // plan's widest precision), allocated at creation when all three axes can
-  // take the matrix-core route; null otherwise
+  // take the matrix-core route; null otherwise.  Only applies enqueued on the
+  // creation stream itself use it (pair_usable in dense.hip)
   void* pair_buf;
+  hipStream_t home;  // the stream of cheb_plan_create
 };
 
 namespace cheb {
@@ -139,7 +141,7 @@ int launch_axis_pass(const cheb_plan* p, int axis, int mode, int first, const T*
 
 // full apply (z, y, x passes) in precision T
 template <typename T>
-int apply_t(const cheb_plan* p, const T* K, const T* u, T* y, int mode, hipStream_t s);
+int apply_t(const cheb_plan* p, const T* K, const T* u, T* y, int mode, hipStream_t s, T* second = nullptr);
 
 // ---- matrix-core route (dense.hip) ----
 int dense_setup(cheb_plan* p);
@@ -158,9 +160,12 @@ int launch_line_pass(const cheb_plan* p, int axis, int mode, int transpose, int 
                      const T* u, T* y, hipStream_t s);
 // the three passes of one apply (mode LINE_REDUCED, LINE_TRANSP, LINE_FULL or,
 // with c[axis], LINE_JAC) when every axis takes the matrix-core route: x and y
-// in one launch where the plan holds pair_buf, then z adding both
+// in one launch where there is a field for the second output -- the caller's
+// (second), else the plan's where it may be used --, then z adding both; without
+// one z, x and y in turn.  The sums have one order: the results are the same bits
 template <typename T>
-int launch_line_apply(const cheb_plan* p, int mode, const T* K, const T* const* c, const T* u, T* y, hipStream_t s);
+int launch_line_apply(const cheb_plan* p, int mode, const T* K, const T* const* c, const T* u, T* y, hipStream_t s,
+                      T* second = nullptr);
 // pi: 0 for the FP64 passes, 1 for the FP32 passes
 inline bool use_dense(const cheb_plan* p, int axis, int pi) {
   if (!p->dd_ok[axis] || p->route == CHEB_ROUTE_FFT) return false;

@@ -129,9 +129,9 @@ int launch_axis_pass(const cheb_plan* p, int axis, int mode, int first, const T*
 }
 
 template <typename T>
-int apply_t(const cheb_plan* p, const T* K, const T* u, T* y, int mode, hipStream_t s) {
+int apply_t(const cheb_plan* p, const T* K, const T* u, T* y, int mode, hipStream_t s, T* second) {
   if (use_dense_all(p, sizeof(T) == sizeof(double) ? 0 : 1))
-    return launch_line_apply<T>(p, line_mode(mode), K, nullptr, u, y, s);
+    return launch_line_apply<T>(p, line_mode(mode), K, nullptr, u, y, s, second);
   // z pass first (it initialises every row it owns), then y, then x
   int rc = launch_axis_pass<T>(p, 2, mode, 1, K, u, y, s);
   if (rc) return rc;

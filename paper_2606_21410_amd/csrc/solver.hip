@@ -418,12 +418,15 @@ int check_K(cheb_plan* p, const void* K, Scratch& sc) {
   return CHEB_OK;
 }
 
-// reduced right-hand side bt = f_k - A_kr H g (interior), 0 on the boundary
+// reduced right-hand side bt = f_k - A_kr H g (interior), 0 on the boundary.
+// Applies within a call write their second partial sum to a free field of the
+// workspace (`second`; null in FP32, which has none), so that a call on any stream
+// takes two launches per apply
 template <typename T>
-int reduced_rhs(cheb_plan* p, const T* K, const T* f, const T* g, T* bt, T* tmp) {
+int reduced_rhs(cheb_plan* p, const T* K, const T* f, const T* g, T* bt, T* tmp, T* second) {
   int rc = fill<T>(tmp, 0.0, p->npts, p->stream);
   if (!rc) rc = lift_full<T>(p, tmp, g, p->stream);
-  if (!rc) rc = apply_t<T>(p, K, tmp, bt, 0, p->stream);
+  if (!rc) rc = apply_t<T>(p, K, tmp, bt, 0, p->stream, second);
   if (!rc) rc = rhs_reduced<T>(bt, f, p->g.n, p->stream);
   return rc;
 }
@@ -442,13 +445,13 @@ int mean_K(cheb_plan* p, const T* K, Scratch& sc, double* kc) {
 }
 
 template <typename T>
-int solve_plain(cheb_plan* p, const T* K, const T* bt, T* x, T* r, KrylovWS<T>& kw, Scratch& sc,
+int solve_plain(cheb_plan* p, const T* K, const T* bt, T* x, T* r, T* second, KrylovWS<T>& kw, Scratch& sc,
                 const SolveParams& sp, int mode, Stats& st, double* relres, int* status) {
   double bnorm;
   int rc = vnorm<T>(p, bt, sc, &bnorm);
   if (rc) return rc;
   const double tol = std::fmax(sp.rtol * bnorm, sp.atol);
-  auto A = [&](const T* in, T* out) { return apply_t<T>(p, K, in, out, mode, p->stream); };
+  auto A = [&](const T* in, T* out) { return apply_t<T>(p, K, in, out, mode, p->stream, second); };
   double res = 0;
   if (bnorm == 0.0) {
     rc = fill<T>(x, 0.0, p->npts, p->stream);
@@ -546,10 +549,10 @@ int newton_directions(cheb_plan* p, const double* T, NewtonWS& w) {
 // epilogues; on the FFT route each axis' term is one accumulating derivative
 // pass that lifts v's interior values in the pencil (as the reduced operator
 // does) and multiplies by c_a.
-int newton_jv(cheb_plan* p, NewtonWS& w, const double* v, double* y) {
+int newton_jv(cheb_plan* p, NewtonWS& w, const double* v, double* y, double* second) {
   hipStream_t s = p->stream;
   const double* c[3] = {w.c[0], w.c[1], w.c[2]};
-  if (use_dense_all(p, 0)) return launch_line_apply<double>(p, LINE_JAC, w.k, c, v, y, s);
+  if (use_dense_all(p, 0)) return launch_line_apply<double>(p, LINE_JAC, w.k, c, v, y, s, second);
   int rc = CHEB_OK;
   for (int a = 2; a >= 0 && !rc; --a) {
     if (use_dense(p, a, 0)) {
@@ -562,9 +565,10 @@ int newton_jv(cheb_plan* p, NewtonWS& w, const double* v, double* y) {
   return rc;
 }
 
-// out = -R(T) = f - sum_a D_a (k D_a T) on interior rows, 0 on boundary rows
+// out = -R(T) = f - sum_a D_a (k D_a T) on interior rows, 0 on boundary rows; c[0],
+// formed after it, is its scratch
 int newton_neg_residual(cheb_plan* p, NewtonWS& w, const double* T, const double* f, double* out) {
-  int rc = apply_t<double>(p, w.k, T, out, 0, p->stream);
+  int rc = apply_t<double>(p, w.k, T, out, 0, p->stream, w.c[0]);
   if (!rc) rc = rhs_reduced<double>(out, f, p->g.n, p->stream);
   return rc;
 }
@@ -626,7 +630,7 @@ int cheb_solve(cheb_plan* plan, const void* K, const void* f, const void* g_face
     rc = check_K(p, K, w.sc);
     if (rc) return rc;
     const double* Kd = (const double*)K;
-    rc = reduced_rhs<double>(p, Kd, (const double*)f, (const double*)g_faces, w.bt, w.t1);
+    rc = reduced_rhs<double>(p, Kd, (const double*)f, (const double*)g_faces, w.bt, w.t1, w.t2);
     if (!rc) {
       if (sp.warm) {
         rc = copy_scale<double>(w.x, (const double*)u_inout, 1.0, p->npts, p->stream);
@@ -635,7 +639,7 @@ int cheb_solve(cheb_plan* plan, const void* K, const void* f, const void* g_face
         rc = fill<double>(w.x, 0.0, p->npts, p->stream);
       }
     }
-    if (!rc) rc = solve_plain<double>(p, Kd, w.bt, w.x, w.r, w.kw, w.sc, sp, 1, st, &relres, &status);
+    if (!rc) rc = solve_plain<double>(p, Kd, w.bt, w.x, w.r, w.t2, w.kw, w.sc, sp, 1, st, &relres, &status);
     if (!rc) rc = copy_scale<double>((double*)u_inout, w.x, 1.0, p->npts, p->stream);
     if (!rc) rc = lift_full<double>(p, (double*)u_inout, (const double*)g_faces, p->stream);
   } else if (p->prec == CHEB_F32) {
@@ -645,7 +649,7 @@ int cheb_solve(cheb_plan* plan, const void* K, const void* f, const void* g_face
     if (rc) return rc;
     const float* Kf = (const float*)K;
     // the first Krylov vector doubles as scratch for the lift of the face data
-    rc = reduced_rhs<float>(p, Kf, (const float*)f, (const float*)g_faces, w.bt, w.kw.w);
+    rc = reduced_rhs<float>(p, Kf, (const float*)f, (const float*)g_faces, w.bt, w.kw.w, nullptr);
     if (!rc) {
       if (sp.warm) {
         rc = copy_scale<float>(w.x, (const float*)u_inout, 1.0, p->npts, p->stream);
@@ -654,7 +658,7 @@ int cheb_solve(cheb_plan* plan, const void* K, const void* f, const void* g_face
         rc = fill<float>(w.x, 0.0, p->npts, p->stream);
       }
     }
-    if (!rc) rc = solve_plain<float>(p, Kf, w.bt, w.x, w.kw.Z, w.kw, w.sc, sp, 1, st, &relres, &status);
+    if (!rc) rc = solve_plain<float>(p, Kf, w.bt, w.x, w.kw.Z, nullptr, w.kw, w.sc, sp, 1, st, &relres, &status);
     if (!rc) rc = copy_scale<float>((float*)u_inout, w.x, 1.0, p->npts, p->stream);
     if (!rc) rc = lift_full<float>(p, (float*)u_inout, (const float*)g_faces, p->stream);
   } else {
@@ -664,7 +668,7 @@ int cheb_solve(cheb_plan* plan, const void* K, const void* f, const void* g_face
     rc = check_K(p, K, w.sc);
     if (rc) return rc;
     const double* Kd = (const double*)K;
-    rc = reduced_rhs<double>(p, Kd, (const double*)f, (const double*)g_faces, w.bt, w.t1);
+    rc = reduced_rhs<double>(p, Kd, (const double*)f, (const double*)g_faces, w.bt, w.t1, w.r);
     if (!rc) rc = cast_f64_f32(w.K32, Kd, 1.0, p->npts, p->stream);
     if (!rc) {
       if (sp.warm) {
@@ -677,8 +681,8 @@ int cheb_solve(cheb_plan* plan, const void* K, const void* f, const void* g_face
     double bnorm = 0;
     if (!rc) rc = vnorm<double>(p, w.bt, w.sc, &bnorm);
     const double tol = std::fmax(sp.rtol * bnorm, sp.atol);
-    auto A64 = [&](const double* in, double* out) { return apply_t<double>(p, Kd, in, out, 1, p->stream); };
-    auto A32 = [&](const float* in, float* out) { return apply_t<float>(p, w.K32, in, out, 1, p->stream); };
+    auto A64 = [&](const double* in, double* out) { return apply_t<double>(p, Kd, in, out, 1, p->stream, w.t1); };
+    auto A32 = [&](const float* in, float* out) { return apply_t<float>(p, w.K32, in, out, 1, p->stream, (float*)w.t1); };
     double kc = 1.0;
     if (!rc && sp.precond) {
       rc = precond_setup(p);
@@ -790,7 +794,7 @@ int cheb_adjoint(cheb_plan* plan, const void* K, const void* u, const void* dLdu
   Stats st;
   double relres = 0;
   int status = CHEB_OK;
-  if (!rc) rc = solve_plain<double>(p, Kd, w.bt, w.x, w.r, w.kw, w.sc, sp, 2, st, &relres, &status);
+  if (!rc) rc = solve_plain<double>(p, Kd, w.bt, w.x, w.r, w.t2, w.kw, w.sc, sp, 2, st, &relres, &status);
   if (!rc) rc = copy_scale<double>((double*)lambda, w.x, 1.0, p->npts, p->stream);
   // gradient  -K sum_a (D_a u)(D_a^T lambda~)
   for (int a = 0; a < 3 && !rc; ++a) {
@@ -936,7 +940,7 @@ int cheb_newton_jacobian(cheb_plan* plan, const void* K0, double alpha, const vo
   rc = newton_coefficients(p, (const double*)K0, alpha, (const double*)T, w);
   if (!rc) rc = newton_directions(p, (const double*)T, w);
   if (!rc) rc = newton_checked(p);  // before the first write to y
-  if (!rc) rc = newton_jv(p, w, (const double*)v, (double*)y);
+  if (!rc) rc = newton_jv(p, w, (const double*)v, (double*)y, w.V);  // k'(T) has served
   if (!rc) rc = hip_check(hipStreamSynchronize(p->stream), "hipStreamSynchronize");
   return rc;
 }
@@ -1002,7 +1006,7 @@ int cheb_newton(cheb_plan* plan, const void* K0, double alpha, const void* f, co
     if (!rc && sp.precond) rc = mean_K<double>(p, w.k, w64.sc, &kc);
     if (!rc) rc = fill<double>(w64.x, 0.0, p->npts, s);
     if (rc) break;
-    auto J = [&](const double* in, double* out) { return newton_jv(p, w, in, out); };
+    auto J = [&](const double* in, double* out) { return newton_jv(p, w, in, out, w.V); };
     auto Mi = [&](const double* in, double* out) {
       return precond_apply<double>(p, in, out, w64.kw.pa, w64.kw.pb, kc, false, s);
     };

@@ -940,7 +940,12 @@ int cheb_newton_jacobian(cheb_plan* plan, const void* K0, double alpha, const vo
   rc = newton_coefficients(p, (const double*)K0, alpha, (const double*)T, w);
   if (!rc) rc = newton_directions(p, (const double*)T, w);
   if (!rc) rc = newton_checked(p);  // before the first write to y
-  if (!rc) rc = newton_jv(p, w, (const double*)v, (double*)y, w.V);  // k'(T) has served
+  if (rc) {
+    // the launches behind the check still read T and write work
+    (void)hipStreamSynchronize(p->stream);
+    return rc;
+  }
+  rc = newton_jv(p, w, (const double*)v, (double*)y, w.V);  // k'(T) has served
   if (!rc) rc = hip_check(hipStreamSynchronize(p->stream), "hipStreamSynchronize");
   return rc;
 }

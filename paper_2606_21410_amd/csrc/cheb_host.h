@@ -4,9 +4,18 @@
 #pragma once
 
 #include <cmath>
+#include <cstddef>
 #include <vector>
 
 namespace cheb {
+
+// Most systems of interior size m that one batched launch of the preconditioner's
+// contractions takes: element offsets in their packed blocks stay below 2^31 and
+// a grid dimension (one system per index) below 2^16; at least one
+inline int batch_slice(const int* m) {
+  const size_t each = (size_t)m[0] * m[1] * m[2], lim = (((size_t)1 << 31) - 1) / each;
+  return (int)(lim < 1 ? 1 : lim < 65535 ? lim : 65535);
+}
 
 // Ascending Chebyshev-Gauss-Lobatto differentiation matrix on an interval of
 // length L (Section 2.2, the collocation derivative at t_j = -cos(pi j / N)):

@@ -1572,12 +1572,9 @@ static int axis_contract(const cheb_plan* p, int a, int dir, bool tr, const int*
   return hip_check(hipGetLastError(), "axis contraction");
 }
 
-// the fused path: every axis on the per-wave kernel, element offsets in the
-// packed blocks below 2^31
-static bool fused_ok(const int* m, int nb) {
-  const size_t lim = (size_t)1 << 31;
-  return m[0] <= 128 && m[1] <= 128 && m[2] <= 128 && (size_t)m[0] * m[1] * m[2] * (size_t)nb < lim;
-}
+// the fused path: every axis at most 128 interior nodes (batches in slices of
+// batch_slice systems)
+static bool fused_ok(const int* m) { return m[0] <= 128 && m[1] <= 128 && m[2] <= 128; }
 
 // The six contractions on the matrix cores with the packing, the eigenvalue
 // scaling and the unpacking folded into the first, the middle and the last
@@ -1691,7 +1688,7 @@ int precond_apply(const cheb_plan* p, const T* in, T* out, T* bufA, T* bufB, dou
                   hipStream_t s) {
   const int n0 = p->g.n[0], n1 = p->g.n[1], n2 = p->g.n[2];
   const int m[3] = {n0 - 2, n1 - 2, n2 - 2};
-  if (fused_ok(m, 1))
+  if (fused_ok(m))
     return precond_fused<T>(p, in, out, bufA, bufB, transpose, 1, nullptr, 1.0 / kc, nullptr, nullptr, nullptr, s);
   const size_t tot = (size_t)m[0] * m[1] * m[2];
   const T* base = pc_base<T>(p);
@@ -1739,9 +1736,19 @@ int precond_apply_batch(const cheb_plan* rep, const T* in, T* out, const long lo
   const int n0 = rep->g.n[0], n1 = rep->g.n[1], n2 = rep->g.n[2];
   const int m[3] = {n0 - 2, n1 - 2, n2 - 2};
   (void)span;
-  if (fused_ok(m, nmem))
-    return precond_fused<T>(rep, in, out, bufA, bufB, false, nmem, offs, 0.0, sys, kc, mem, s);
   const size_t tot = (size_t)m[0] * m[1] * m[2];
+  if (fused_ok(m)) {
+    // only these kernels read tables per system (mem): a group of any size takes
+    // them, in slices
+    const int most = batch_slice(m);
+    for (int k = 0; k < nmem; k += most) {
+      const int nb = nmem - k < most ? nmem - k : most;
+      if (int rc = precond_fused<T>(rep, in, out, bufA + k * tot, bufB + k * tot, false, nb, offs + k, 0.0, sys + k, kc,
+                                    mem, s))
+        return rc;
+    }
+    return CHEB_OK;
+  }
   const T* base = pc_base<T>(rep);
   hipLaunchKernelGGL(k_pack_interior_b<T>, dim3(grid1(tot), nmem), dim3(256), 0, s, in, offs, bufA, n0, n1, n2);
   int rc = hip_check(hipGetLastError(), "batched pack");

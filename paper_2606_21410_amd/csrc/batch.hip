@@ -943,10 +943,28 @@ int cheb_batch_create(const cheb_grid* grids, int32_t nprob, int32_t precision, 
     cheb_batch_destroy(B);
     return code;
   };
+  // systems of one size and box (the face types may differ)
+  auto same_box = [&](int a, int b) {
+    for (int d = 0; d < 3; ++d)
+      if (grids[a].n[d] != grids[b].n[d] || grids[a].lo[d] != grids[b].lo[d] || grids[a].hi[d] != grids[b].hi[d])
+        return false;
+    return true;
+  };
+  // their plans read the first one's operator tables, and none keeps a field for a
+  // second partial sum: the batched passes add in place, and the right-hand sides
+  // take the workspace's
+  std::vector<int> boxes;
   size_t P = 0;
   for (int s = 0; s < nprob; ++s) {
+    const cheb_plan* box = nullptr;
+    for (int q : boxes)
+      if (same_box(q, s)) {
+        box = B->plans[q];
+        break;
+      }
+    if (!box) boxes.push_back(s);
     cheb_plan* p = nullptr;
-    rc = cheb_plan_create(&grids[s], precision, stream, &p);
+    rc = plan_create(&grids[s], precision, stream, box, false, &p);
     if (rc) return fail(rc);
     B->plans.push_back(p);
     B->off.push_back(P);
@@ -954,13 +972,7 @@ int cheb_batch_create(const cheb_grid* grids, int32_t nprob, int32_t precision, 
     P += round_up(p->npts, 64);
   }
   B->P = P;
-  // apply groups: identical sizes and boxes (the face types may differ)
-  auto same_box = [&](int a, int b) {
-    for (int d = 0; d < 3; ++d)
-      if (grids[a].n[d] != grids[b].n[d] || grids[a].lo[d] != grids[b].lo[d] || grids[a].hi[d] != grids[b].hi[d])
-        return false;
-    return true;
-  };
+  // apply groups: a box each
   bool any_merged = false;
   for (int s = 0; s < nprob; ++s) {
     bool placed = false;
@@ -1206,7 +1218,7 @@ int cheb_batch_solve(cheb_batch* batch, const void* const* K, const void* const*
     if (B->koff[s] == o) rc = copy_scale<double>(w.K64 + o, Ks, 1.0, p->npts, st);
     if (!rc) rc = fill<double>(w.t1 + o, 0.0, p->npts, st);
     if (!rc) rc = lift_full<double>(p, w.t1 + o, (const double*)g_faces[s], st);
-    if (!rc) rc = apply_t<double>(p, Ks, w.t1 + o, w.bt + o, 0, st);
+    if (!rc) rc = apply_t<double>(p, Ks, w.t1 + o, w.bt + o, 0, st, w.r + o);
     if (!rc) rc = rhs_reduced<double>(w.bt + o, (const double*)f[s], p->g.n, st);
     if (!rc && bp.warm) {
       rc = copy_scale<double>(w.x + o, (const double*)u_inout[s], 1.0, p->npts, st);

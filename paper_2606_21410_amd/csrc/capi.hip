@@ -66,87 +66,14 @@ void cc_weights(int N, double L, std::vector<double>& w) {
   for (double& x : w) x *= L / 2.0;
 }
 
-}  // namespace
-}  // namespace cheb
-
-using namespace cheb;
-
-namespace {
-
-// Time one reduced apply configuration: 2 warm-up applies, then `reps` timed
-// with events on the plan's stream; returns microseconds per apply.
-template <typename T>
-static int time_apply(cheb_plan* p, const T* K, const T* u, T* y, int reps, double* us) {
-  hipEvent_t e0 = nullptr, e1 = nullptr;
-  int rc = hip_check(hipEventCreate(&e0), "hipEventCreate");
-  if (!rc) rc = hip_check(hipEventCreate(&e1), "hipEventCreate");
-  for (int i = 0; !rc && i < 2; ++i) rc = apply_t<T>(p, K, u, y, 1, p->stream);
-  if (!rc) rc = hip_check(hipEventRecord(e0, p->stream), "hipEventRecord");
-  for (int i = 0; !rc && i < reps; ++i) rc = apply_t<T>(p, K, u, y, 1, p->stream);
-  if (!rc) rc = hip_check(hipEventRecord(e1, p->stream), "hipEventRecord");
-  if (!rc) rc = hip_check(hipEventSynchronize(e1), "hipEventSynchronize");
-  float ms = 0.f;
-  if (!rc) rc = hip_check(hipEventElapsedTime(&ms, e0, e1), "hipEventElapsedTime");
-  if (e0) (void)hipEventDestroy(e0);
-  if (e1) (void)hipEventDestroy(e1);
-  *us = 1e3 * ms / reps;
-  return rc;
+void free_tables(cheb_plan* p) {
+  if (p->dd64 && !p->dd_lent) (void)hipFree(p->dd64);
+  if (p->dd32 && !p->dd_lent) (void)hipFree(p->dd32);
 }
-
-template <typename T>
-static int autotune_t(cheb_plan* p, const T* K, const T* u, T* y, double* report, int report_len) {
-  const int pi = sizeof(T) == sizeof(double) ? 0 : 1;
-  const int saved_route = p->route;
-  int saved_var[3];
-  for (int a = 0; a < 3; ++a) saved_var[a] = p->dense_var[a][pi];
-  bool any = false;
-  for (int a = 0; a < 3; ++a) any = any || p->dd_ok[a];
-  double t[3] = {-1.0, -1.0, -1.0};  // FFT route, matrix route tile shape 0, tile shape 1
-  int rc = CHEB_OK;
-  p->route = CHEB_ROUTE_FFT;
-  rc = time_apply<T>(p, K, u, y, 10, &t[0]);
-  for (int v = 0; !rc && any && v < 2; ++v) {
-    p->route = CHEB_ROUTE_MATRIX;
-    for (int a = 0; a < 3; ++a) p->dense_var[a][pi] = v;
-    rc = time_apply<T>(p, K, u, y, 10, &t[1 + v]);
-  }
-  p->route = saved_route;
-  if (rc) {
-    for (int a = 0; a < 3; ++a) p->dense_var[a][pi] = saved_var[a];
-    return rc;
-  }
-  int best = 0;
-  for (int c = 1; c < 3; ++c)
-    if (t[c] >= 0.0 && t[c] < t[best]) best = c;
-  p->auto_fft[pi] = best == 0;
-  for (int a = 0; a < 3; ++a) p->dense_var[a][pi] = best == 0 ? saved_var[a] : best - 1;
-  for (int c = 0; c < 3 && c < report_len; ++c) report[c] = t[c];
-  if (report_len > 3) report[3] = best;
-  return CHEB_OK;
-}
-
 }  // namespace
 
-extern "C" {
-
-const char* cheb_last_error(void) { return g_last_error.c_str(); }
-
-const char* cheb_status_string(int status) {
-  switch (status) {
-    case CHEB_OK: return "ok";
-    case CHEB_NOT_CONVERGED: return "not converged";
-    case CHEB_STAGNATED: return "stagnated";
-    case CHEB_ERR_INVALID_ARG: return "invalid argument";
-    case CHEB_ERR_SINGULAR_BC: return "singular boundary conditions (all faces Neumann)";
-    case CHEB_ERR_BAD_INPUT: return "bad input (NaN/Inf or non-positive conductivity)";
-    case CHEB_ERR_DEVICE: return "device error";
-    case CHEB_ERR_WORKSPACE: return "workspace missing or too small";
-    case CHEB_ERR_UNSUPPORTED: return "unsupported";
-    default: return "unknown status";
-  }
-}
-
-int cheb_plan_create(const cheb_grid* grid, int32_t precision, void* stream, cheb_plan** out) {
+int plan_create(const cheb_grid* grid, int32_t precision, void* stream, const cheb_plan* box, bool second,
+                cheb_plan** out) {
   if (!grid || !out) {
     set_error("null argument");
     return CHEB_ERR_INVALID_ARG;
@@ -250,7 +177,7 @@ int cheb_plan_create(const cheb_grid* grid, int32_t precision, void* stream, che
   if (!rc)
     rc = hip_check(hipMemcpy(p->dconst32, h32.data(), cnt * sizeof(float), hipMemcpyHostToDevice),
                    "hipMemcpy(plan constants)");
-  if (!rc) rc = dense_setup(p);
+  if (!rc) rc = dense_setup(p, box, second);
   p->hpinned_len = 4096;
   if (!rc)
     rc = hip_check(hipHostMalloc((void**)&p->hpinned, p->hpinned_len * sizeof(double), hipHostMallocDefault),
@@ -258,8 +185,7 @@ int cheb_plan_create(const cheb_grid* grid, int32_t precision, void* stream, che
   if (rc) {
     if (p->dconst64) (void)hipFree(p->dconst64);
     if (p->dconst32) (void)hipFree(p->dconst32);
-    if (p->dd64) (void)hipFree(p->dd64);
-    if (p->dd32) (void)hipFree(p->dd32);
+    free_tables(p);
     if (p->pair_buf) (void)hipFree(p->pair_buf);
     if (p->hpinned) (void)hipHostFree(p->hpinned);
     delete p;
@@ -267,6 +193,89 @@ int cheb_plan_create(const cheb_grid* grid, int32_t precision, void* stream, che
   }
   *out = p;
   return CHEB_OK;
+}
+
+}  // namespace cheb
+
+using namespace cheb;
+
+namespace {
+
+// Time one reduced apply configuration: 2 warm-up applies, then `reps` timed
+// with events on the plan's stream; returns microseconds per apply.
+template <typename T>
+static int time_apply(cheb_plan* p, const T* K, const T* u, T* y, int reps, double* us) {
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  int rc = hip_check(hipEventCreate(&e0), "hipEventCreate");
+  if (!rc) rc = hip_check(hipEventCreate(&e1), "hipEventCreate");
+  for (int i = 0; !rc && i < 2; ++i) rc = apply_t<T>(p, K, u, y, 1, p->stream);
+  if (!rc) rc = hip_check(hipEventRecord(e0, p->stream), "hipEventRecord");
+  for (int i = 0; !rc && i < reps; ++i) rc = apply_t<T>(p, K, u, y, 1, p->stream);
+  if (!rc) rc = hip_check(hipEventRecord(e1, p->stream), "hipEventRecord");
+  if (!rc) rc = hip_check(hipEventSynchronize(e1), "hipEventSynchronize");
+  float ms = 0.f;
+  if (!rc) rc = hip_check(hipEventElapsedTime(&ms, e0, e1), "hipEventElapsedTime");
+  if (e0) (void)hipEventDestroy(e0);
+  if (e1) (void)hipEventDestroy(e1);
+  *us = 1e3 * ms / reps;
+  return rc;
+}
+
+template <typename T>
+static int autotune_t(cheb_plan* p, const T* K, const T* u, T* y, double* report, int report_len) {
+  const int pi = sizeof(T) == sizeof(double) ? 0 : 1;
+  const int saved_route = p->route;
+  int saved_var[3];
+  for (int a = 0; a < 3; ++a) saved_var[a] = p->dense_var[a][pi];
+  bool any = false;
+  for (int a = 0; a < 3; ++a) any = any || p->dd_ok[a];
+  double t[3] = {-1.0, -1.0, -1.0};  // FFT route, matrix route tile shape 0, tile shape 1
+  int rc = CHEB_OK;
+  p->route = CHEB_ROUTE_FFT;
+  rc = time_apply<T>(p, K, u, y, 10, &t[0]);
+  for (int v = 0; !rc && any && v < 2; ++v) {
+    p->route = CHEB_ROUTE_MATRIX;
+    for (int a = 0; a < 3; ++a) p->dense_var[a][pi] = v;
+    rc = time_apply<T>(p, K, u, y, 10, &t[1 + v]);
+  }
+  p->route = saved_route;
+  if (rc) {
+    for (int a = 0; a < 3; ++a) p->dense_var[a][pi] = saved_var[a];
+    return rc;
+  }
+  int best = 0;
+  for (int c = 1; c < 3; ++c)
+    if (t[c] >= 0.0 && t[c] < t[best]) best = c;
+  p->auto_fft[pi] = best == 0;
+  for (int a = 0; a < 3; ++a) p->dense_var[a][pi] = best == 0 ? saved_var[a] : best - 1;
+  for (int c = 0; c < 3 && c < report_len; ++c) report[c] = t[c];
+  if (report_len > 3) report[3] = best;
+  return CHEB_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+const char* cheb_last_error(void) { return g_last_error.c_str(); }
+
+const char* cheb_status_string(int status) {
+  switch (status) {
+    case CHEB_OK: return "ok";
+    case CHEB_NOT_CONVERGED: return "not converged";
+    case CHEB_STAGNATED: return "stagnated";
+    case CHEB_ERR_INVALID_ARG: return "invalid argument";
+    case CHEB_ERR_SINGULAR_BC: return "singular boundary conditions (all faces Neumann)";
+    case CHEB_ERR_BAD_INPUT: return "bad input (NaN/Inf or non-positive conductivity)";
+    case CHEB_ERR_DEVICE: return "device error";
+    case CHEB_ERR_WORKSPACE: return "workspace missing or too small";
+    case CHEB_ERR_UNSUPPORTED: return "unsupported";
+    default: return "unknown status";
+  }
+}
+
+int cheb_plan_create(const cheb_grid* grid, int32_t precision, void* stream, cheb_plan** out) {
+  return plan_create(grid, precision, stream, nullptr, true, out);
 }
 
 int cheb_plan_set_workspace(cheb_plan* plan, void* dev_ptr, size_t bytes) {
@@ -449,8 +458,7 @@ int cheb_plan_destroy(cheb_plan* plan) {
   if (!plan) return CHEB_OK;
   if (plan->dconst64) (void)hipFree(plan->dconst64);
   if (plan->dconst32) (void)hipFree(plan->dconst32);
-  if (plan->dd64) (void)hipFree(plan->dd64);
-  if (plan->dd32) (void)hipFree(plan->dd32);
+  free_tables(plan);
   if (plan->pair_buf) (void)hipFree(plan->pair_buf);
   if (plan->kev_ok) {
     (void)hipEventDestroy(plan->kev[0]);

@@ -242,7 +242,21 @@ template int launch_dense_batch<double>(const cheb_plan*, int, int, const double
 template int launch_dense_batch<float>(const cheb_plan*, int, int, const float*, const float*, float*, const DenseSys*,
                                        const int*, int, hipStream_t);
 
-int dense_setup(cheb_plan* p) {
+int dense_setup(cheb_plan* p, const cheb_plan* box, bool second) {
+  if (box) {
+    for (int a = 0; a < 3; ++a) {
+      p->dd_mt[a] = box->dd_mt[a];
+      p->dd_ok[a] = box->dd_ok[a];
+      for (int q = 0; q < 2; ++q) {
+        p->dd_off[a][q] = box->dd_off[a][q];
+        p->dense_var[a][q] = box->dense_var[a][q];
+      }
+    }
+    p->dd64 = box->dd64;
+    p->dd32 = box->dd32;
+    p->dd_lent = 1;
+    return CHEB_OK;
+  }
   size_t total = 0;
   int src[3];
   for (int a = 0; a < 3; ++a) p->dd_mt[a] = line_mt(p->ax[a].N);
@@ -313,7 +327,7 @@ int dense_setup(cheb_plan* p) {
   // second output of the two-axis launch (x and y passes together), for plans
   // whose three axes can all take the matrix-core route; optional: without it
   // an apply takes three launches
-  if (!rc && p->dd_ok[0] && p->dd_ok[1] && p->dd_ok[2]) {
+  if (!rc && second && p->dd_ok[0] && p->dd_ok[1] && p->dd_ok[2]) {
     const size_t bytes = p->npts * (p->prec == CHEB_F32 ? sizeof(float) : sizeof(double));
     if (hipMalloc(&p->pair_buf, bytes) != hipSuccess) {
       (void)hipGetLastError();

@@ -95,6 +95,7 @@ struct cheb_plan {
   int dd_ok[3];
   size_t dd_off[3][2];
   int dd_mt[3];         // row blocks of the axis' tables (dense_pass.h)
+  int dd_lent;          // the tables belong to another plan
   int dense_var[3][2];  // tile shape of the matrix-core pass, [axis][f64, f32]
   int auto_fft[2];      // CHEB_ROUTE_AUTO resolved to the FFT route, [f64, f32] (autotuner)
   hipEvent_t kev[2];    // LGMRES: completion of the last two enqueued Arnoldi steps (created on first use)
@@ -143,8 +144,14 @@ int launch_axis_pass(const cheb_plan* p, int axis, int mode, int first, const T*
 template <typename T>
 int apply_t(const cheb_plan* p, const T* K, const T* u, T* y, int mode, hipStream_t s, T* second = nullptr);
 
+// cheb_plan_create; box and second as in dense_setup
+int plan_create(const cheb_grid* grid, int32_t precision, void* stream, const cheb_plan* box, bool second,
+                cheb_plan** out);
+
 // ---- matrix-core route (dense.hip) ----
-int dense_setup(cheb_plan* p);
+// box: a plan of the same grid sizes, box, Robin coefficients and precision that
+// outlives p and lends it its tables (null: p's own); second: allocate pair_buf
+int dense_setup(cheb_plan* p, const cheb_plan* box, bool second);
 struct DenseSys;
 // batched reduced pass over the systems act[0..nact) of the table sys (same n
 // and box as `rep`); K, u, y are packed bases

@@ -206,8 +206,9 @@ int cheb_plan_set_route(cheb_plan* plan, int32_t route);
 int cheb_plan_autotune(cheb_plan* plan, int32_t field_precision, const void* K, const void* u, void* y,
                        double* report, int32_t report_len);
 
-/* Tile shape of the matrix-core route's reduced passes for one precision, on
- * every axis with N <= 128 (longer axes have one shape): 0 = 8-wave workgroups
+/* Tile shape of the matrix-core route's reduced passes for one precision, where
+ * a wave owns its pencils: axes with N <= 128 unless the launch is small or an
+ * axis beside them longer (those have one shape).  0 = 8-wave workgroups
  * (one copy of the derivative's fragment table serves eight 16-pencil tasks),
  * 1 = 4-wave workgroups (the two shapes the autotuner times).
  * field_precision: CHEB_F64 or CHEB_F32 (the passes that run in that type).

@@ -88,6 +88,11 @@ const double* robin_array<double>(const cheb_plan* p) { return p->rn64; }
 template <>
 const float* robin_array<float>(const cheb_plan* p) { return p->rn32; }
 
+// whether the x and y passes of an apply can share a launch
+bool share_launch(const cheb_plan* p, int pi) {
+  return p->dd_ok[0] && p->dd_ok[1] && p->dd_mt[0] == p->dd_mt[1] && p->dense_var[0][pi] == p->dense_var[1][pi];
+}
+
 // the launch fields of one axis: tables, lift entries, per-node inverses, output
 template <typename T>
 LineAxis<T> line_axis(const cheb_plan* p, int axis, int mode, int transpose, bool batch, T* y, T* yb) {
@@ -126,6 +131,7 @@ LineArgs<T> line_args(const cheb_plan* p, const T* K, const T* u, const DenseSys
   a.bcmask = bc_mask(p->g.bc);
   a.nseg = 1;
   a.wpw = 0;
+  a.tasks = 0;
   a.yadd = nullptr;
   return a;
 }
@@ -134,6 +140,12 @@ template <typename T>
 int dispatch_line(const cheb_plan* p, LineArgs<T>& a, int mode, int first, hipStream_t s) {
   const int axis = a.ax[0].axis, shape = p->dense_var[axis][prec_index<T>()];
   const int mt = p->dd_mt[axis];
+  const bool der = mode == LINE_DERIV || mode == LINE_DMUL;
+  const int o = der || mode == LINE_FULL ? 0 : 2;
+  auto tasks = [&](int x) {
+    return ((a.n[x == 0 ? 1 : 0] - o) * (a.n[x == 2 ? 1 : 2] - o) + 15) / 16;
+  };
+  a.tasks = axis < 2 && !der && share_launch(p, prec_index<T>()) ? tasks(0) + tasks(1) : tasks(axis);
   switch (mt) {
     case 1: return launch_line_mt<T, 1>(a, mode, first, shape, s);
     case 2: return launch_line_mt<T, 2>(a, mode, first, shape, s);
@@ -189,8 +201,7 @@ int launch_line_apply(const cheb_plan* p, int mode, const T* K, const T* const* 
   const int pi = prec_index<T>();
   // the x and y passes share a launch, each into its own output
   T* y1 = nullptr;
-  if (p->dd_mt[0] == p->dd_mt[1] && p->dense_var[0][pi] == p->dense_var[1][pi])
-    y1 = second ? second : pair_usable(p, s) ? (T*)p->pair_buf : nullptr;
+  if (share_launch(p, pi)) y1 = second ? second : pair_usable(p, s) ? (T*)p->pair_buf : nullptr;
   if (y1) {
     LineArgs<T> a = line_args<T>(p, K, u, nullptr, nullptr, 0);
     a.nseg = 2;

@@ -159,24 +159,58 @@ static int launch_wave_nw(LineArgs<T>& a, int mode, int first, hipStream_t s) {
 }
 
 template <typename T, int MT>
+static int launch_pass_modes(LineArgs<T>& a, int mode, int first, hipStream_t s) {
+  switch (mode) {
+    case LINE_REDUCED: return launch_line_g<T, MT, LINE_REDUCED>(a, first, s);
+    case LINE_TRANSP: return launch_line_g<T, MT, LINE_TRANSP>(a, first, s);
+    case LINE_FULL: return launch_line_g<T, MT, LINE_FULL>(a, first, s);
+    case LINE_DERIV: return launch_line_g<T, MT, LINE_DERIV>(a, first, s);
+    case LINE_JAC:
+      if constexpr (sizeof(T) == sizeof(double)) return launch_line_g<T, MT, LINE_JAC>(a, first, s);
+      break;
+    case LINE_DMUL:
+      if constexpr (sizeof(T) == sizeof(double)) return launch_line_g<T, MT, LINE_DMUL>(a, first, s);
+      break;
+  }
+  set_error("matrix-core pass: bad mode");
+  return CHEB_ERR_INVALID_ARG;
+}
+
+// Three and four row blocks with at most one task per CU (a.tasks: of the pass, or
+// of both axes that can share a launch, so that the choice is the same whether they
+// do) go to k_line_pass: its four waves share a task's products, where k_line_wave
+// would leave three of a CU's four SIMDs idle.  FP64, one launch of 4 to 250 tasks,
+// N = 128: 8.7-13 us against 14.4-16; N = 96: 7.6-9.8 against 9.8-11.6; from about
+// 400 tasks on k_line_wave is faster, and with two row blocks it always is.  Batches
+// keep k_line_wave: their task count changes as systems finish, and the two differ
+// in the rounding of a lone middle row.
+template <typename T>
+static int launch_few(const LineArgs<T>& a, bool* few) {
+  static DeviceCache cache;
+  int dev = 0;
+  *few = false;
+  if (a.sys) return CHEB_OK;
+  if (int rc = current_device(&dev)) return rc;
+  int cus = cache.v[dev].load(std::memory_order_relaxed);
+  if (cus == 0) {
+    if (int rc = hip_check(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), "CU count")) return rc;
+    cache.v[dev].store(cus, std::memory_order_relaxed);
+  }
+  *few = a.tasks <= cus;
+  return CHEB_OK;
+}
+
+template <typename T, int MT>
 int launch_line_mt(LineArgs<T>& a, int mode, int first, int shape, hipStream_t s) {
   if constexpr (MT <= kWaveMaxMT) {
+    if constexpr (MT >= 3) {
+      bool few = false;
+      if (int rc = launch_few<T>(a, &few)) return rc;
+      if (few) return launch_pass_modes<T, MT>(a, mode, first, s);
+    }
     return shape == 0 ? launch_wave_nw<T, MT, 8>(a, mode, first, s) : launch_wave_nw<T, MT, 4>(a, mode, first, s);
   } else {
-    switch (mode) {
-      case LINE_REDUCED: return launch_line_g<T, MT, LINE_REDUCED>(a, first, s);
-      case LINE_TRANSP: return launch_line_g<T, MT, LINE_TRANSP>(a, first, s);
-      case LINE_FULL: return launch_line_g<T, MT, LINE_FULL>(a, first, s);
-      case LINE_DERIV: return launch_line_g<T, MT, LINE_DERIV>(a, first, s);
-      case LINE_JAC:
-        if constexpr (sizeof(T) == sizeof(double)) return launch_line_g<T, MT, LINE_JAC>(a, first, s);
-        break;
-      case LINE_DMUL:
-        if constexpr (sizeof(T) == sizeof(double)) return launch_line_g<T, MT, LINE_DMUL>(a, first, s);
-        break;
-    }
-    set_error("matrix-core pass: bad mode");
-    return CHEB_ERR_INVALID_ARG;
+    return launch_pass_modes<T, MT>(a, mode, first, s);
   }
 }
 

@@ -27,10 +27,11 @@
 // argument; the kernel is compiled per number of row blocks MT, and rows and
 // k-steps past R meet zero fragments.
 //
-// Two kernels: up to four row blocks (N <= 128) one wave computes every row of
-// its pencils (line_wave.h); past that the fragments and accumulators of one
-// wave do not fit its registers, and k_line_pass below gives each wave of a
-// workgroup one row block, with the split tile shared through LDS.
+// Two kernels.  With up to four row blocks one wave computes every row of its
+// pencils (line_wave.h).  Past that the fragments and accumulators of one wave do
+// not fit its registers, and k_line_pass below gives each wave of a workgroup one
+// row block, with the split tile shared through LDS; launches of few tasks on
+// three or four row blocks take it too (launch_line_mt).
 //
 // k_line_pass: only that operand, e / o, is in LDS.  What belongs to an output
 // row (K, C, the partial sums y, the stores) goes between memory and the
@@ -193,6 +194,7 @@ struct LineArgs {
   // multiple of 16)
   int nseg;
   int wpw;  // k_line_wave: waves of a workgroup that take tasks
+  int tasks;  // 16-pencil tasks of the launch, of x and y together where they can share one
   // accumulating pass along the unit-stride axis: y += yadd + this pass (yadd
   // is the second output of a two-axis launch); unused by the other passes
   const T* yadd;
@@ -281,7 +283,14 @@ __global__ __launch_bounds__(64 * MT, line_waves<T>(MT)) void k_line_pass(LineAr
   const int R = line_pairs(N), KO = (N & 1) ? R : R - 1;
   const bool midv = line_midv(N, MT);
   const int RM = midv ? R - 1 : R;            // rows on the matrix cores
-  const int nke = (R + 3) >> 2, nko = (KO + 3) >> 2;
+  // steps that hold columns of the axis (in the FP32 order of line_kmap a block's
+  // four steps share its columns)
+  constexpr bool K32 = sizeof(T) == sizeof(float) && MT <= kWaveMaxMT;
+  auto steps = [&](int cols) {
+    const int last = cols - 16 * (MT - 1);
+    return !K32 ? (cols + 3) >> 2 : last > 16 ? KS + 1 : KS - 4 + min(max(last, 0), 4);
+  };
+  const int nke = steps(R), nko = steps(KO);
   const int half = N >> 1;
   const int n0 = a.n[0], n1 = a.n[1], n2 = a.n[2];
   const int stride = CG ? 1 : axis == 1 ? n2 : n1 * n2;
@@ -541,11 +550,14 @@ __global__ __launch_bounds__(64 * MT, line_waves<T>(MT)) void k_line_pass(LineAr
       // the operands of the step two ahead are read while a step multiplies; the
       // scheduling barriers keep it so (left alone, the compiler reads the whole
       // column ahead and runs out of registers)
-      const T* Ue = U + lk * SC + li;
+      // row line_kmap(ks, lk); of the middle row's step only lane group 0 meets
+      // entries that are not zero
+      const T* Ue = U + (K32 ? 4 * lk : lk) * SC + li;
       T be[3], bo[3];
       auto operands = [&](int ks) {
-        be[ks % 3] = Ue[ks * 4 * SC];
-        if (ks < KS) bo[ks % 3] = Ue[OB + ks * 4 * SC];
+        const int k0 = K32 ? line_kmap(ks, 0, true) : 4 * ks;
+        be[ks % 3] = Ue[k0 * SC];
+        if (ks < KS) bo[ks % 3] = Ue[OB + k0 * SC];
       };
       operands(0);
       operands(1);

@@ -362,8 +362,7 @@ bool eig_centro(int m, const std::vector<double>& A, std::vector<double>& lam, s
 // device kernels
 // ---------------------------------------------------------------------------
 
-// D(i, c) = sum_k A(i, k) B(k, c) per batch, arbitrary element strides; one
-// wave computes a 16 x 64 tile with four 16x16 MFMA accumulators.
+// D(i, c) = sum_k A(i, k) B(k, c) per batch, arbitrary element strides
 struct GemmArgs {
   const void* A;
   const void* B;
@@ -374,46 +373,7 @@ struct GemmArgs {
   int ps;                      // k_axis_gemm_lds: the symmetric half, ceil(m / 2)
 };
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_axis_gemm(GemmArgs g) {
-  typedef typename Mfma<T>::v4 v4;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int i0 = blockIdx.x * 16;
-  const int c0 = (blockIdx.y * 4 + wave) * 64;
-  const int b = blockIdx.z;
-  const T* A = (const T*)g.A + b * g.a_sb;
-  const T* B = (const T*)g.B + b * g.b_sb;
-  T* D = (T*)g.D + b * g.d_sb;
-  if (c0 >= g.C) return;
-  const int li = lane & 15, lk = lane >> 4;  // A operand: row li, k lk; B operand: k lk, column li
-  v4 acc[4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t) acc[t] = v4{0, 0, 0, 0};
-  const int ia = i0 + li;
-  for (int k0 = 0; k0 < g.Kd; k0 += 4) {
-    const int k = k0 + lk;
-    const T av = (ia < g.I && k < g.Kd) ? A[ia * g.a_si + k * g.a_sk] : T(0);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int c = c0 + t * 16 + li;
-      const T bv = (c < g.C && k < g.Kd) ? B[k * g.b_sk + c * g.b_sc] : T(0);
-      acc[t] = Mfma<T>::mac(av, bv, acc[t]);
-    }
-  }
-  // lane holds column lane%16 of each 16x16 block; rows per Mfma<T>::row
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const int c = c0 + t * 16 + li;
-    if (c >= g.C) continue;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = i0 + Mfma<T>::row(lk, r);
-      if (i < g.I) D[i * g.d_si + c * g.d_sc] = acc[t][r];
-    }
-  }
-}
-
-// The same contraction staged through LDS, plain (KIND 0) or, for an axis whose
+// The contraction staged through LDS, plain (KIND 0) or, for an axis whose
 // 1-D operator is centro-symmetric (m = ps + ph, ps = ceil(m/2)), with half the
 // multiply-adds.  With Q the symmetric / antisymmetric node-pair basis:
 //   KIND 1 (the input enters through Q^T, e.g. V^{-1} = diag(Vs^{-1}, Vw^{-1}) Q^T):
@@ -1715,7 +1675,7 @@ int precond_apply(const cheb_plan* p, const T* in, T* out, T* bufA, T* bufB, dou
   return hip_check(hipGetLastError(), "unpack");
 }
 
-// plain GEMM on the matrix cores, exposed for the layout test:
+// the long axes' contraction kernel as a plain GEMM, exposed for the layout test:
 // D (I x C) = A (I x K) B (K x C), all row-major
 template <typename T>
 int mfma_gemm(const T* A, const T* B, T* D, int I, int K, int C, hipStream_t s) {
@@ -1724,8 +1684,9 @@ int mfma_gemm(const T* A, const T* B, T* D, int I, int K, int C, hipStream_t s) 
   g.I = I; g.Kd = K; g.C = C;
   g.a_si = K; g.a_sk = 1; g.b_sk = C; g.b_sc = 1; g.d_si = C; g.d_sc = 1;
   g.a_sb = g.b_sb = g.d_sb = 0;
-  dim3 grid((I + 15) / 16, (C + 255) / 256, 1);
-  hipLaunchKernelGGL(k_axis_gemm<T>, grid, dim3(256), 0, s, g);
+  g.ps = 0;
+  dim3 grid((I + kGt - 1) / kGt, (C + kGt - 1) / kGt, 1);
+  hipLaunchKernelGGL((k_axis_gemm_lds<T, 0, false>), grid, dim3(256), 0, s, g);
   return hip_check(hipGetLastError(), "mfma gemm");
 }
 

@@ -1,5 +1,6 @@
 // Matrix-core route: the fragment tables of D and D^T written into the plan,
 // and the launches of the axis passes.
+#include <cstdlib>
 #include <vector>
 
 #include "cheb_host.h"
@@ -66,15 +67,11 @@ void line_table(int N, int mts, bool f32, const AxisConst& c, F m, double* tab) 
 }
 
 template <typename T>
-const T* line_table_of(const cheb_plan* p, int axis, int transpose);
+const T* tables(const cheb_plan* p);
 template <>
-const double* line_table_of<double>(const cheb_plan* p, int axis, int transpose) {
-  return p->dd64 + p->dd_off[axis][transpose];
-}
+const double* tables<double>(const cheb_plan* p) { return p->dd64; }
 template <>
-const float* line_table_of<float>(const cheb_plan* p, int axis, int transpose) {
-  return p->dd32 + p->dd_off[axis][transpose];
-}
+const float* tables<float>(const cheb_plan* p) { return p->dd32; }
 
 template <typename T>
 constexpr int prec_index() {
@@ -88,17 +85,28 @@ const double* robin_array<double>(const cheb_plan* p) { return p->rn64; }
 template <>
 const float* robin_array<float>(const cheb_plan* p) { return p->rn32; }
 
+bool is_deriv(int mode) { return mode == LINE_DERIV || mode == LINE_DMUL; }
+
+// whether a pass along the axis reads its tables of one block more
+bool raised_pass(const cheb_plan* p, int axis, int mode, bool batch, int pi) {
+  return p->raised == axis + 1 && p->raised_use[pi] && !batch && !is_deriv(mode);
+}
+int pass_blocks(const cheb_plan* p, int axis, int mode, bool batch, int pi) {
+  return p->dd_mt[axis] + (raised_pass(p, axis, mode, batch, pi) ? 1 : 0);
+}
+
 // whether the x and y passes of an apply can share a launch
 bool share_launch(const cheb_plan* p, int pi) {
-  return p->dd_ok[0] && p->dd_ok[1] && p->dd_mt[0] == p->dd_mt[1] && p->dense_var[0][pi] == p->dense_var[1][pi];
+  return p->dd_ok[0] && p->dd_ok[1] && p->dense_var[0][pi] == p->dense_var[1][pi] &&
+         pass_blocks(p, 0, LINE_REDUCED, false, pi) == pass_blocks(p, 1, LINE_REDUCED, false, pi);
 }
 
 // the launch fields of one axis: tables, lift entries, per-node inverses, output
 template <typename T>
 LineAxis<T> line_axis(const cheb_plan* p, int axis, int mode, int transpose, bool batch, T* y, T* yb) {
-  const bool all = mode == LINE_FULL || mode == LINE_DERIV || mode == LINE_DMUL;  // every pencil, not only the interior ones
+  const bool all = mode == LINE_FULL || is_deriv(mode);  // every pencil, not only the interior ones
   LineAxis<T> x;
-  x.tab = line_table_of<T>(p, axis, transpose);
+  x.tab = tables<T>(p) + (raised_pass(p, axis, mode, batch, prec_index<T>()) ? p->raised_off : p->dd_off[axis])[transpose];
   x.y = y;
   x.yb = yb;
   x.c = nullptr;
@@ -139,8 +147,8 @@ LineArgs<T> line_args(const cheb_plan* p, const T* K, const T* u, const DenseSys
 template <typename T>
 int dispatch_line(const cheb_plan* p, LineArgs<T>& a, int mode, int first, hipStream_t s) {
   const int axis = a.ax[0].axis, shape = p->dense_var[axis][prec_index<T>()];
-  const int mt = p->dd_mt[axis];
-  const bool der = mode == LINE_DERIV || mode == LINE_DMUL;
+  const int mt = pass_blocks(p, axis, mode, a.sys != nullptr, prec_index<T>());
+  const bool der = is_deriv(mode);
   const int o = der || mode == LINE_FULL ? 0 : 2;
   auto tasks = [&](int x) {
     return ((a.n[x == 0 ? 1 : 0] - o) * (a.n[x == 2 ? 1 : 2] - o) + 15) / 16;
@@ -263,6 +271,11 @@ int dense_setup(cheb_plan* p, const cheb_plan* box, bool second) {
         p->dense_var[a][q] = box->dense_var[a][q];
       }
     }
+    p->raised = box->raised;
+    for (int q = 0; q < 2; ++q) {
+      p->raised_use[q] = box->raised_use[q];
+      p->raised_off[q] = box->raised_off[q];
+    }
     p->dd64 = box->dd64;
     p->dd32 = box->dd32;
     p->dd_lent = 1;
@@ -270,13 +283,8 @@ int dense_setup(cheb_plan* p, const cheb_plan* box, bool second) {
   }
   size_t total = 0;
   int src[3];
-  for (int a = 0; a < 3; ++a) p->dd_mt[a] = line_mt(p->ax[a].N);
-  // the x and y passes share a launch when their tables have the same number of
-  // row blocks; a table with one block fewer is written with an idle block for
-  // that (a third launch costs more than the idle wave)
-  if (p->dd_mt[0] - p->dd_mt[1] == 1 && line_supported(p->ax[0].N)) p->dd_mt[1] = p->dd_mt[0];
-  if (p->dd_mt[1] - p->dd_mt[0] == 1 && line_supported(p->ax[1].N)) p->dd_mt[0] = p->dd_mt[1];
   for (int a = 0; a < 3; ++a) {
+    p->dd_mt[a] = line_mt(p->ax[a].N);
     p->dd_ok[a] = line_supported(p->ax[a].N) ? 1 : 0;
     // default tile shape (16 pencils per tile); cheb_plan_autotune replaces it
     // by timing
@@ -286,7 +294,7 @@ int dense_setup(cheb_plan* p, const cheb_plan* box, bool second) {
     src[a] = a;
     for (int b = 0; b < a; ++b)
       if (p->ax[b].N == p->ax[a].N && p->ax[b].L == p->ax[a].L && p->ax[b].m00 == p->ax[a].m00 &&
-          p->ax[b].mNN == p->ax[a].mNN && p->dd_mt[b] == p->dd_mt[a]) {
+          p->ax[b].mNN == p->ax[a].mNN) {
         src[a] = b;
         break;
       }
@@ -299,6 +307,29 @@ int dense_setup(cheb_plan* p, const cheb_plan* box, bool second) {
       if (p->dd_ok[a]) total += round_up((size_t)line_tab(p->dd_mt[a]).size, 64);
     }
   }
+  // The x and y passes share a launch when their tables have the same number of
+  // row blocks.  An axis with one block fewer has a second pair of tables with an
+  // idle block, for the applies (derivatives run alone): a third launch costs more.
+  // 33x65x65 FP64 15.5 us against 19.6, 97x129x129 48 against 51, 161x193x33 41
+  // against 53; FP32 12.7 against 16.5, 29.7 against 35, 26 against 38.  From four
+  // blocks to five the axis also changes kernels, from a wave to a task to a wave to
+  // a row block, which in FP64 only small grids stand: x and y of 116 tasks
+  // (140x128x9) 18.9 us against 26.2, of 477 (150x100x33) 33.3 against 35.2, of 1000
+  // (131x127x65) 45.3 against 46.4 but of 1568 (160x100x100) 80 against 63, of 2050
+  // (130x129x130) 95 against 84; FP32 gains at every size (150x129x129 48 against 53).
+  p->raised = 0;
+  if (p->dd_ok[0] && p->dd_ok[1] && p->dd_ok[2] && std::abs(p->dd_mt[0] - p->dd_mt[1]) == 1) {
+    const int a = p->dd_mt[0] < p->dd_mt[1] ? 0 : 1;
+    const int* n = p->g.n;
+    const int tasks = ((n[1] - 2) * (n[2] - 2) + 15) / 16 + ((n[0] - 2) * (n[2] - 2) + 15) / 16;
+    p->raised = a + 1;
+    p->raised_use[0] = p->dd_mt[a] != kWaveMaxMT || tasks <= 1024;
+    p->raised_use[1] = 1;
+    for (int t = 0; t < 2; ++t) {
+      p->raised_off[t] = total;
+      total += round_up((size_t)line_tab(p->dd_mt[a] + 1).size, 64);
+    }
+  }
   p->dd64 = nullptr;
   p->dd32 = nullptr;
   if (total == 0) return CHEB_OK;
@@ -307,15 +338,15 @@ int dense_setup(cheb_plan* p, const cheb_plan* box, bool second) {
     if (p->dd_ok[a] && src[a] == a) dense_D(p->ax[a].N, p->ax[a].L, D[a]);
   auto fill = [&](bool f32, std::vector<double>& h) {
     h.resize(total);
-    for (int a = 0; a < 3; ++a) {
-      if (!p->dd_ok[a] || src[a] != a) continue;
+    auto pair = [&](int a, int mt, const size_t* off) {
       const int N = p->ax[a].N, n = N + 1;
-      const double* M = D[a].data();
-      line_table(N, p->dd_mt[a], f32, p->ax[a], [=](int i, int j) { return M[(size_t)i * n + j]; },
-                 h.data() + p->dd_off[a][0]);
-      line_table(N, p->dd_mt[a], f32, p->ax[a], [=](int i, int j) { return M[(size_t)j * n + i]; },
-                 h.data() + p->dd_off[a][1]);
-    }
+      const double* M = D[src[a]].data();
+      line_table(N, mt, f32, p->ax[a], [=](int i, int j) { return M[(size_t)i * n + j]; }, h.data() + off[0]);
+      line_table(N, mt, f32, p->ax[a], [=](int i, int j) { return M[(size_t)j * n + i]; }, h.data() + off[1]);
+    };
+    for (int a = 0; a < 3; ++a)
+      if (p->dd_ok[a] && src[a] == a) pair(a, p->dd_mt[a], p->dd_off[a]);
+    if (p->raised) pair(p->raised - 1, p->dd_mt[p->raised - 1] + 1, p->raised_off);
   };
   // each precision that the plan's passes run in
   int rc = CHEB_OK;

@@ -95,6 +95,9 @@ struct cheb_plan {
   int dd_ok[3];
   size_t dd_off[3][2];
   int dd_mt[3];         // row blocks of the axis' tables (dense_pass.h)
+  int raised;           // axis + 1 with further tables of one block more, for applies (0: none; dense_setup)
+  int raised_use[2];    // whether applies take them, [f64, f32]
+  size_t raised_off[2];
   int dd_lent;          // the tables belong to another plan
   int dense_var[3][2];  // tile shape of the matrix-core pass, [axis][f64, f32]
   int auto_fft[2];      // CHEB_ROUTE_AUTO resolved to the FFT route, [f64, f32] (autotuner)

@@ -36,11 +36,11 @@ static int launch_line_inst(const LineArgs<T>& a, hipStream_t s) {
     const int ta = axis == 0 ? a.n[1] : a.n[0], tb = axis == 2 ? a.n[1] : a.n[2];
     return ((ta - o) * (tb - o) + 15) / 16 * (a.sys ? a.nact : 1);
   };
-  // Workgroups per CU: the fewest rounds of tiles, weighted by what a round
-  // takes, which grows with the workgroups that share the CU (about 2 + W for W
-  // of them, from the phase times at 129^3: a tile alone 9k cycles, of three
-  // 20k).  Two per CU instead of three take the z pass of 129^3, 1009 tiles,
-  // in two full rounds.
+  // Workgroups per CU where several fit (five and six row blocks in FP32, and
+  // derivatives; an FP64 product holds one): the fewest rounds of tiles, weighted by
+  // what a round takes, about 2 + W for W workgroups that share the CU.  Against as
+  // many as fit: apply 161x161x65 FP32 31.3 us and 35.9, 130^3 47.7 and 50.1,
+  // 145x145x257 93 and 101; nowhere slower over 16 grids from 65 to 257 nodes.
   auto per_cu_of = [&](int tiles) {
     const int cus = resident >> 8, occ = resident & 255;
     int best = 1, cost = 1 << 30;

@@ -79,8 +79,11 @@ static int launch_line_g(const LineArgs<T>& a, int first, hipStream_t s) {
 }
 
 // k_line_wave: persistent over the XCDs' task ranges, a grid of whole XCD
-// rounds.  Few tasks are spread one to a CU before a workgroup takes more than
-// one wave's worth.
+// rounds.  Few tasks are spread over the CUs before a workgroup takes more than one
+// wave's worth (a wave more than that everywhere: 129^3 FP64 51 us, 56 with half as
+// many), and it takes a wave more where the rounding to whole XCD rounds would
+// otherwise give some CUs a second workgroup: 121x81x61, 731 tasks, three waves in
+// 304 workgroups 33.6 us FP64 and 21.5 FP32, four in 224 25.9 and 17.5.
 template <typename T, int MT, int MODE, bool FIRST, bool CG, int NW>
 static int launch_wave_inst(LineArgs<T>& a, hipStream_t s) {
   constexpr int lds = wave_lds_bytes<T>(MT, NW, CG);
@@ -112,11 +115,14 @@ static int launch_wave_inst(LineArgs<T>& a, hipStream_t s) {
     return ((ta - o) * (tb - o) + 15) / 16 * (a.sys ? a.nact : 1);
   };
   const int t0 = tasks_of(a.ax[0].axis), t1 = a.nseg == 2 ? tasks_of(a.ax[1].axis) : 0;
-  const int wpw = (t0 + t1 + cus - 1) / cus;
-  a.wpw = wpw < NW ? (wpw > 0 ? wpw : 1) : NW;
-  // workgroups per XCD and segment
+  // workgroups per XCD and segment with w tasks each at a time
   const int most = t0 > t1 ? t0 : t1;
-  int g = ((most + 7) / 8 + a.wpw - 1) / a.wpw;
+  auto groups = [&](int w) { return ((most + 7) / 8 + w - 1) / w; };
+  int w = (t0 + t1 + cus - 1) / cus;
+  if (w < 1) w = 1;
+  while (w < NW && 8 * groups(w) * a.nseg > cus) ++w;
+  a.wpw = w < NW ? w : NW;
+  int g = groups(a.wpw);
   const int cap = cus * occ / 8 / a.nseg;
   if (g > cap) g = cap;
   if (g < 1) g = 1;

@@ -131,8 +131,8 @@ __device__ __forceinline__ void block_sum(double (&v)[G], double* red) {
 // The kernels over a basis hold the loads of kBE elements of several vectors in
 // flight together (indices past the chunk are clamped, vectors past the last one
 // read an operand again); a load at a time per element left them waiting on memory:
-// at 27 systems of 49^3 to 65^3 in FP32 (5M points, 6 vectors) the dots took 49 us and
-// the update 44, now 13 each.
+// at nine systems of 49^3, 57^3 and 65^3 in FP32 (1.7M points, 6 vectors) the dots
+// took 49 us and the update 44, now 13 each.
 constexpr int kBE = 4;
 
 // partials[chunk][i] = <V_i, w> over the chunk for i < nv, <w, w> for i = nv;
@@ -425,7 +425,8 @@ int bdots(cheb_batch* B, const T* V, size_t ld, int nv, const T* w, BScratch& sc
   int rc = hip_check(hipGetLastError(), "batched multi-dot");
   if (rc) return rc;
   // the sums go straight to pinned host memory: a copy behind them is one more
-  // dependent launch in every step (27 systems of 49^3 to 65^3, whole solve: 14.6 ms with it, 12.8 without)
+  // dependent launch in every step (nine systems of 49^3 to 65^3, whole solve:
+  // 14.6 ms with it, 12.8 without)
   double* hp = B->hpin + (size_t)2 * B->nprob * (kMaxCoef + 8);
   hipLaunchKernelGGL(k_breduce, dim3(B->nprob), dim3(kBT), 0, B->stream, sc.partials, nv1, B->sys_c0, B->sys_nc,
                      hp, kMaxCoef);

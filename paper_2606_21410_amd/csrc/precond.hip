@@ -1586,7 +1586,7 @@ static int precond_fused(const cheb_plan* p, const T* in, T* out, T* bufA, T* bu
   };
   // Planes that fit in LDS (the rule of plane_ok; a y axis that is not
   // mirror-symmetric fits up to 64 nodes): three launches.  An axis at a time takes
-  // five, each streaming the field: 129^3 FP64 82 us against 63, 49^3 29 against
+  // five, each streaming the field: 129^3 FP64 82 us against 58, 49^3 29 against
   // 20, 33^3 24 against 18, 129^3 FP32 64 against 42.
   const bool sy = p->pc_ax[1].split, sz = p->pc_ax[2].split;
   if (plane_ok<T>(m[1], m[2], sy, sz)) {

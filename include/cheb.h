@@ -143,7 +143,8 @@ typedef struct cheb_plan cheb_plan;
  * (cheb_plan_set_stream), those recorded into a graph, and all of them if that
  * allocation failed take three launches (or the caller's scratch:
  * cheb_apply_scratch) and share no memory, so a plan's applies may be in flight
- * on several streams.  The results are the same bits.
+ * on several streams.  With three launches the last bit may differ at the middle
+ * node along z where N is 32, 64, 96 or 128; other results are the same bits.
  * Nothing is allocated after creation except where a call says so. */
 int cheb_plan_create(const cheb_grid* grid, int32_t precision, void* stream, cheb_plan** out);
 
@@ -231,9 +232,10 @@ int cheb_apply(cheb_plan* plan, const void* K, const void* u, void* y, uint32_t 
 /* cheb_apply with the caller's scratch field (n0*n1*n2 values of y's type, not
  * overlapping K, u or y; its contents are undefined afterwards) in place of the
  * plan's second output, so that an apply on any stream or in a graph takes two
- * launches.  The same results, bit for bit.  scratch follows the rules of every
- * buffer: alive until the stream, or the last replay, has finished with it, and
- * not shared by applies that may run at the same time. */
+ * launches: the results of cheb_apply on the creation stream, bit for bit.
+ * scratch follows the rules of every buffer: alive until the stream, or the last
+ * replay, has finished with it, and not shared by applies that may run at the same
+ * time. */
 int cheb_apply_scratch(cheb_plan* plan, const void* K, const void* u, void* y, uint32_t flags, void* scratch);
 
 /* Solve div(K grad u) = f with face data g (Algorithm 2): build the reduced

@@ -228,7 +228,8 @@ int launch_line_apply(const cheb_plan* p, int mode, const T* K, const T* const* 
     a.ax[1] = a.ax[0];
     return dispatch_line<T>(p, a, mode, 0, s);
   }
-  // (z + x) + y, as above
+  // (z + x) + y, as above (the one-wave kernel adds a lone middle row along z as z +
+  // (x + y) there: the last bit may differ)
   for (int axis : {2, 0, 1})
     if (int rc = launch_line_pass<T>(p, axis, mode, tr, axis == 2, K, c ? c[axis] : nullptr, u, y, s)) return rc;
   return CHEB_OK;

@@ -172,7 +172,8 @@ int launch_line_pass(const cheb_plan* p, int axis, int mode, int transpose, int 
 // with c[axis], LINE_JAC) when every axis takes the matrix-core route: x and y
 // in one launch where there is a field for the second output -- the caller's
 // (second), else the plan's where it may be used --, then z adding both; without
-// one z, x and y in turn.  The sums have one order: the results are the same bits
+// one z, x and y in turn, in the same order of addition but for a lone middle row
+// along z (N = 32, 64, 96, 128)
 template <typename T>
 int launch_line_apply(const cheb_plan* p, int mode, const T* K, const T* const* c, const T* u, T* y, hipStream_t s,
                       T* second = nullptr);

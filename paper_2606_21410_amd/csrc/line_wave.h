@@ -308,7 +308,7 @@ __global__ __launch_bounds__(64 * NW, wave_simd_waves<T>(MT, MODE, NW)) void k_l
     renew();
 
     // store one block's rows: nodes i and N - i
-    T ylo[FIRST ? 1 : KS], yhi[FIRST ? 1 : KS], zlo[YADD ? 8 : 1], zhi[YADD ? 8 : 1], ymid = T(0), zmid = T(0);
+    T ylo[FIRST ? 1 : KS], yhi[FIRST ? 1 : KS], zlo[YADD ? 8 : 1], zhi[YADD ? 8 : 1], ymid = T(0);
     auto store = [&](int m, T (&lo)[4], T (&hi)[4]) __attribute__((always_inline)) {
       to_lines(lo);
       to_lines(hi);
@@ -474,7 +474,7 @@ __global__ __launch_bounds__(64 * NW, wave_simd_waves<T>(MT, MODE, NW)) void k_l
           yhi[FIRST ? 0 : ks] = at(py, ks / 4, ks % 4, true);
         } else {
           ymid = dense_at(py, b0 + __mul24(half, st));
-          if (YADD) zmid = dense_at(a.yadd, b0 + __mul24(half, st));
+          if (YADD) ymid += dense_at(a.yadd, b0 + __mul24(half, st));
           if (YADD) load_z(0);
         }
       });
@@ -509,9 +509,7 @@ __global__ __launch_bounds__(64 * NW, wave_simd_waves<T>(MT, MODE, NW)) void k_l
       if (midv && valid && lk == 0 && (!FULL || (fl & PF_TIN))) {
         T m = mid;
         if (tl) m -= u0 * dc0[half] + uN * dcN[half];
-        if (!FIRST) m += ymid;
-        if (YADD) m += zmid;
-        dense_ref(py, b0 + __mul24(half, st)) = m;
+        dense_ref(py, b0 + __mul24(half, st)) = FIRST ? m : m + ymid;
       }
     }
     if (task + t_step < t_end) {
